@@ -104,6 +104,26 @@ __device__ __forceinline__ void f6_from_codes(const float *q, uint32_t w[6]) {
     for (int i = 0; i < 6; ++i) w[i] = (uint32_t)r[i];
 }
 
+// the same from 32 codes held as exact fp16 pairs (codes 2i, 2i + 1 in p[i]);
+// element i goes to field i
+typedef _Float16 f6_v32h __attribute__((ext_vector_type(32)));
+typedef _Float16 f6_v2h __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t f6_half_pair(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(a, b));
+}
+__device__ __forceinline__ void f6_from_half_codes(const uint32_t (&p)[16], uint32_t w[6]) {
+    f6_v32h h;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const f6_v2h t = __builtin_bit_cast(f6_v2h, p[i]);
+        h[2 * i] = t[0];
+        h[2 * i + 1] = t[1];
+    }
+    const auto r = __builtin_amdgcn_cvt_scalef32_pk32_fp6_f16(h, 1.0f);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) w[i] = (uint32_t)r[i];
+}
+
 // the inverse: six fp6 dwords -> four dwords of nibbles
 __device__ __forceinline__ void nibbles_from_f6(const uint32_t w[6], uint32_t d[4]) {
 #pragma unroll

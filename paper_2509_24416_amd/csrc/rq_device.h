@@ -50,6 +50,12 @@ __device__ __forceinline__ void stage1_pair(uint32_t u, uint32_t v, float &sum, 
     asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel_hi:[1,0,1]" : "=v"(dif) : "v"(u), "v"(v));
 }
 
+// and from the high halves
+__device__ __forceinline__ void stage1_pair_hi(uint32_t u, uint32_t v, float &sum, float &dif) {
+    asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[1,0,1] op_sel_hi:[1,0,1]" : "=v"(sum) : "v"(u), "v"(v));
+    asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,1] op_sel_hi:[1,0,1]" : "=v"(dif) : "v"(u), "v"(v));
+}
+
 // Largest |x| of a block: one three-operand max per pair of elements, in two
 // independent chains (a max is exact, so the order does not matter).
 template <int B>
@@ -61,6 +67,143 @@ __device__ __forceinline__ float block_absmax(const float *x) {
         m1 = fmaxf(fmaxf(m1, fabsf(x[i + 2])), fabsf(x[i + 3]));
     }
     return fmaxf(m0, m1);
+}
+
+// ---- rotation spread over lanes: 8 columns per lane ---------------------------
+// A lane holds 8 consecutive columns (a 16-byte chunk) and a Hadamard block of
+// b columns is b / 8 consecutive chunks of neighbouring lanes.  Stages h = 1,
+// 2, 4 stay inside the lane; stage h = 8 << k pairs the chunks whose index
+// differs in bit k.  Lane permutes that cost nothing extra (DPP operands) exist
+// for the lane masks 1, 2, 7 and 8, so chunk bits 0..3 are laid over lanes by
+// those masks: lane l of an octet holds logical chunk l for l < 4 and l ^ 3
+// above.
+//
+// A stage is one fma per element on both sides: with p the partner's value and
+// c = +1 (low side) or -1 (high side), x + c p is u + v on the low side and
+// -(u - v) on the high side.  Each value is thus the butterfly's up to a sign
+// that depends on the lane alone (the product of its c's); magnitudes and
+// roundings are those of u + v and u - v in the same stage order.
+constexpr int kLaneXor1 = 0xB1, kLaneXor2 = 0x4E;   // DPP controls
+constexpr int kQuadLane0 = 0x00, kQuadLane1 = 0x55, kQuadLane2 = 0xAA, kQuadLane3 = 0xFF;
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t lane_xchg(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ float lane_xchg(float v) {
+    return __uint_as_float(lane_xchg<CTRL>(__float_as_uint(v)));
+}
+
+__device__ __forceinline__ int logical_lane(int l) { return l ^ ((l & 4) ? 3 : 0); }
+
+struct CrossSigns {
+    float c8, c16, c32, c64;   // the stages' c
+    float sign;                // butterfly value = sign * computed value
+};
+template <int B>
+__device__ __forceinline__ CrossSigns cross_signs(int chunk) {
+    CrossSigns s;
+    s.c8 = (chunk & 1) ? -1.0f : 1.0f;
+    s.c16 = (chunk & 2) ? -1.0f : 1.0f;
+    s.c32 = (chunk & 4) ? -1.0f : 1.0f;
+    s.c64 = (chunk & 8) ? -1.0f : 1.0f;
+    s.sign = s.c8 * s.c16;
+    if constexpr (B >= 64) s.sign *= s.c32;
+    if constexpr (B >= 128) s.sign *= s.c64;
+    return s;
+}
+
+// stages h = 2, 4 of a lane's eight values (h = 1 is fused with the widening)
+__device__ __forceinline__ void fwht8_rest(float (&x)[8]) {
+#pragma unroll
+    for (int h = 2; h < 8; h <<= 1)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if ((i & h) == 0) {
+                const float u = x[i], v = x[i + h];
+                x[i] = u + v;
+                x[i + h] = u - v;
+            }
+}
+
+// One cross-lane stage of a row's eight values.  The compiler does not fold a
+// lane permute into the fma, so it is written out; a DPP operand must not have
+// been written by the two instructions before (the s_nop covers the entry, the
+// eight independent fmas the rest).
+#define CLQ_CROSS(NAME, DPP)                                                                                  \
+    __device__ __forceinline__ void NAME(float (&x)[8], float c) {                                           \
+        asm("s_nop 1\n\t"                                                                                    \
+            "v_fmac_f32_dpp %0, %0, %8 " DPP " row_mask:0xf bank_mask:0xf\n\t"                               \
+            "v_fmac_f32_dpp %1, %1, %8 " DPP " row_mask:0xf bank_mask:0xf\n\t"                               \
+            "v_fmac_f32_dpp %2, %2, %8 " DPP " row_mask:0xf bank_mask:0xf\n\t"                               \
+            "v_fmac_f32_dpp %3, %3, %8 " DPP " row_mask:0xf bank_mask:0xf\n\t"                               \
+            "v_fmac_f32_dpp %4, %4, %8 " DPP " row_mask:0xf bank_mask:0xf\n\t"                               \
+            "v_fmac_f32_dpp %5, %5, %8 " DPP " row_mask:0xf bank_mask:0xf\n\t"                               \
+            "v_fmac_f32_dpp %6, %6, %8 " DPP " row_mask:0xf bank_mask:0xf\n\t"                               \
+            "v_fmac_f32_dpp %7, %7, %8 " DPP " row_mask:0xf bank_mask:0xf"                                   \
+            : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]) \
+            : "v"(c));                                                                                       \
+    }
+CLQ_CROSS(cross_xor1, "quad_perm:[1,0,3,2]")
+CLQ_CROSS(cross_xor2, "quad_perm:[2,3,0,1]")
+CLQ_CROSS(cross_xor7, "row_half_mirror")
+CLQ_CROSS(cross_xor8, "row_ror:8")
+#undef CLQ_CROSS
+
+// stages h = 8 .. B / 2 of R rows' chunks (every lane of a 16-lane row takes part)
+template <int B, int R>
+__device__ __forceinline__ void cross_stages(float (&x)[R][8], const CrossSigns &s) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) cross_xor1(x[r], s.c8);
+#pragma unroll
+    for (int r = 0; r < R; ++r) cross_xor2(x[r], s.c16);
+    if constexpr (B >= 64) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) cross_xor7(x[r], s.c32);
+    }
+    if constexpr (B >= 128) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) cross_xor8(x[r], s.c64);
+    }
+}
+
+// four maxima (not negative, no NaN) over an octet of lanes, in each of them
+__device__ __forceinline__ void octet_max(float (&m)[4]) {
+    asm("s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %2, %2, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %3, %3, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %2, %2, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %3, %3, %3 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %2, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %3, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xf"
+        : "+v"(m[0]), "+v"(m[1]), "+v"(m[2]), "+v"(m[3]));
+}
+
+// byte 0 of four dwords
+__device__ __forceinline__ uint32_t low_bytes4(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+    const uint32_t ab = __builtin_amdgcn_perm(b, a, 0x0c0c0400u);
+    const uint32_t cd = __builtin_amdgcn_perm(d, c, 0x0c0c0400u);
+    return __builtin_amdgcn_perm(cd, ab, 0x05040100u);
+}
+
+// four rows' 8 columns -> per column the four rows' halves side by side
+// (column e in q[2e], q[2e + 1])
+__device__ __forceinline__ void interleave_rows(const uint4 (&v)[4], uint32_t (&q)[16]) {
+    const uint32_t w[4][4] = {{v[0].x, v[0].y, v[0].z, v[0].w}, {v[1].x, v[1].y, v[1].z, v[1].w},
+                              {v[2].x, v[2].y, v[2].z, v[2].w}, {v[3].x, v[3].y, v[3].z, v[3].w}};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+        q[2 * e] = __builtin_amdgcn_perm(w[1][e >> 1], w[0][e >> 1], sel);
+        q[2 * e + 1] = __builtin_amdgcn_perm(w[3][e >> 1], w[2][e >> 1], sel);
+    }
 }
 
 // Packs eight quantized words (code + 8 in bits 0..3, bits 4..21 clear) into

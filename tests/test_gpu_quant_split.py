@@ -1,0 +1,55 @@
+"""GPU parity of the rotate+quantize kernel at the edges of its split.
+
+A lane owns 8 columns of four rows; the widths below change how many four-row
+groups share a workgroup (1, 2, 4, 8, groups that end inside a wave), how many
+chunks a lane holds (one up to 8192 columns, two up to 16384, none beyond) and
+where a gathered row is staged.  Codes and scales match the CPU oracle bit for
+bit, padding rows hold zero codes.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def clq():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2509_24416_amd as m
+    return m
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.cpu().numpy()
+
+
+@pytest.mark.parametrize("with_perm", [False, True])
+@pytest.mark.parametrize("M,K,block", [
+    (1, 64, 32), (2049, 64, 64), (4100, 192, 32), (1030, 576, 64), (2100, 1152, 64), (4100, 1152, 128),
+    (35, 8192, 128), (33, 8256, 64), (31, 8320, 128), (5, 16384, 32), (3, 16448, 64), (2, 32768, 128)])
+def test_codes_and_scales(clq, M, K, block, with_perm):
+    print(f"\n[gpu case] {M} x {K}, block {block}, perm {with_perm}", flush=True)
+    X = workloads.activations(M, K, "L1", seed=M + K + block)
+    perm = workloads.random_perm(K, seed=K) if with_perm else None
+    pd = None if perm is None else dev(perm)
+    for bits, act, uns in ((4, clq.clq_rotate_quant_act, lambda q, R: clq.clq_unswizzle_act(q, R, K)),
+                           (6, clq.clq_rotate_quant_act_f6, lambda q, R: clq.clq_unswizzle_f6(q, R, K, False)),
+                           (8, clq.clq_rotate_quant_act8, lambda q, R: clq.clq_unswizzle_act8(q, R, K))):
+        rows = (M + 31) // 32 * 32
+        q, s = act(dev(X), block, perm=pd)
+        ref_q, ref_c, ref_s = oracle.quantize_act(X, block, perm, bits=8 if bits == 8 else 4)
+        got = host(uns(q, rows))
+        assert np.array_equal(host(s), ref_s), bits
+        assert np.array_equal(got[:M], ref_c if bits == 8 else ref_q), bits
+        assert not got[M:].any(), bits
