@@ -183,13 +183,15 @@ hipError_t launch_gemm(const uint8_t *Xq, const float *xs, const uint8_t *Wq,
                        int K, void *Y, int64_t ldy, bool i32out, void *workspace,
                        hipStream_t stream, int force);
 
-// The same product, reduced to the squared error against an fp32 target:
-// partials[t] (t < gemm_err_partials(M, N)) receives the fp64 sum of
+// The same product, reduced to the squared error against an fp32 target, for
+// nc candidate weights (candidate c's codes and scales at c * wq_stride bytes
+// and c * ws_stride floats): partials[c * P + t], t < P =
+// gemm_err_partials(M, N), receives the fp64 sum of
 // (Y0 - sum * x_scale * w_scale)^2 over one wave's part of one output tile.
 int64_t gemm_err_partials(int64_t M, int64_t N);
-hipError_t launch_gemm_err(const uint8_t *Xq, const float *xs, const uint8_t *Wq, const float *ws,
-                           int64_t M, int64_t N, int K, const float *Y0, int64_t ldy0, double *partials,
-                           hipStream_t stream);
+hipError_t launch_gemm_err(const uint8_t *Xq, const float *xs, const uint8_t *Wq, const float *ws, int nc,
+                           int64_t wq_stride, int64_t ws_stride, int64_t M, int64_t N, int K, const float *Y0,
+                           int64_t ldy0, double *partials, hipStream_t stream);
 
 // fp6 (e2m3) code layouts: packed int4 units (1 KB) of weights or
 // activations converted unit for unit into fp6 units (1536 bytes, same lane

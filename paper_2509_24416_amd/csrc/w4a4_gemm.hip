@@ -180,6 +180,8 @@ struct GemmArgs {
     const float *y0;
     int64_t ldy0;
     double *errp;
+    int err_nc;            // squared-error mode: candidate weights of this launch,
+    int64_t err_wq, err_ws, err_p;   // and the strides between their codes, scales and partials
 };
 
 // ERR: instead of storing Y, the epilogue sums (Y0 - sum * x_scale * w_scale)^2
@@ -228,7 +230,9 @@ __global__ void __launch_bounds__(C::NT, C::WGS) w4a4_gemm_kernel(GemmArgs a)
     // later one gets about 40% of the unit's tiles: nb rounds for every
     // workgroup, the remaining rr tiles for the first half only.
     const int H = gx >> 1;
-    const bool asym = S == 0 && G == a.full_grid && cnt >= 4 * gx;
+    // Not in the squared-error mode (a 4096 x 3456 x 1152 search of 20 candidates:
+    // 438 us with it, 421 without).
+    const bool asym = !ERR && S == 0 && G == a.full_grid && cnt >= 4 * gx;
     int nb = 0, rr = 0;
     if (asym) {
         nb = min(cnt / gx, (cnt * 2 * 40 + gx * 50) / (gx * 100));
@@ -281,13 +285,22 @@ __global__ void __launch_bounds__(C::NT, C::WGS) w4a4_gemm_kernel(GemmArgs a)
     int edst[EPW > 0 ? EPW : 1];
     auto p_setup = [&]() {
         int tm, tn;
-        coords(pc.L, tm, tn);
+        const uint8_t *wq = a.Wq;
+        const float *wsc = a.ws;
+        if constexpr (ERR) {
+            const int t = pc.L / a.err_nc, c = pc.L - t * a.err_nc;
+            coords(t, tm, tn);
+            wq += c * a.err_wq;
+            wsc += c * a.err_ws;
+        } else {
+            coords(pc.L, tm, tn);
+        }
 #pragma unroll
         for (int j = 0; j < C::UPW; ++j) {
             const int u = wave * C::UPW + j;
             if (u < C::W_UNITS) {
                 const int ug = min(tn * C::W_UNITS + u, wunits_total - 1);
-                usrc[j] = a.Wq + (int64_t)ug * nks * 1024;
+                usrc[j] = wq + (int64_t)ug * nks * 1024;
             } else {
                 const int ux = min(tm * C::X_UNITS + (u - C::W_UNITS), xunits_total - 1);
                 usrc[j] = a.Xq + (int64_t)ux * nks * 1024;
@@ -301,7 +314,7 @@ __global__ void __launch_bounds__(C::NT, C::WGS) w4a4_gemm_kernel(GemmArgs a)
                 edst[j] = E_XS + c * 256;
             } else if (c < C::XS_CH + C::WS_CH || c >= E_CH) {
                 const int w = (c - C::XS_CH) % C::WS_CH;
-                esrc[j] = reinterpret_cast<const uint8_t *>(a.ws + min(tn * C::BN + w * 64 + lane, N - 1));
+                esrc[j] = reinterpret_cast<const uint8_t *>(wsc + min(tn * C::BN + w * 64 + lane, N - 1));
                 edst[j] = E_WS + w * 256;
             } else {
                 const int b = c - C::XS_CH - C::WS_CH;
@@ -562,7 +575,7 @@ __global__ void __launch_bounds__(C::NT, C::WGS) w4a4_gemm_kernel(GemmArgs a)
     // operand units); one explicit wait per channel fragment orders their use.
     auto epilogue = [&](int L, int sj, auto qc) {
         int tm, tn;
-        coords(L, tm, tn);
+        coords(ERR ? L / a.err_nc : L, tm, tn);
         uint32_t lx = (uint32_t)((wm * C::FM * 32 + (lane & 31)) * 4);
         uint32_t lw = (uint32_t)((wn * C::FN * 32 + h16) * 4);
         asm volatile("" : "+v"(lx), "+v"(lw));
@@ -655,7 +668,8 @@ __global__ void __launch_bounds__(C::NT, C::WGS) w4a4_gemm_kernel(GemmArgs a)
                         }
                     }
                 } else if constexpr (ERR) {
-                    // the exact integer sum is x >> 8; d = Y0 - ((sum * x_scale) * w_scale)
+                    // d = Y0 - (sum * x_scale) * w_scale, the integer sum exact
+                    // (x is 256 times it, so the scale takes 1 / 256)
                     if (m < M && n0 < N) {
                         const float *yr = a.y0 + (int64_t)m * a.ldy0 + n0;
                         float yv[16];
@@ -672,12 +686,12 @@ __global__ void __launch_bounds__(C::NT, C::WGS) w4a4_gemm_kernel(GemmArgs a)
 #pragma unroll
                             for (int v = 0; v < 16; ++v) yv[v] = n0 + v < N ? yr[v] : 0.0f;
                         }
-                        const double xm = (double)xsm[fm];
+                        const double xm = (double)xsm[fm] * (1.0 / 256.0);
 #pragma unroll
                         for (int v = 0; v < 16; ++v) {
                             if (RAGGED && n0 + v >= N) continue;
-                            const double d = (double)yv[v] - (double)(x[v] >> 8) * xm * (double)wsv[v];
-                            esum += d * d;
+                            const double d = __builtin_fma(-((double)x[v] * xm), (double)wsv[v], (double)yv[v]);
+                            esum = __builtin_fma(d, d, esum);
                         }
                     }
                 } else {
@@ -703,7 +717,8 @@ __global__ void __launch_bounds__(C::NT, C::WGS) w4a4_gemm_kernel(GemmArgs a)
         if constexpr (ERR) {
             // fixed butterfly over the wave; lane 0 holds the wave's partial
             for (int off = 32; off > 0; off >>= 1) esum += __shfl_xor(esum, off);
-            if (lane == 0) a.errp[(int64_t)L * C::NW + wave] = esum;
+            const int t = L / a.err_nc, c = L - t * a.err_nc;
+            if (lane == 0) a.errp[c * a.err_p + (int64_t)t * C::NW + wave] = esum;
         }
     };
 
@@ -1227,7 +1242,7 @@ void plan_persistent(int ntiles, int nks, bool may_split, int &dp, int &sk, int 
 template <class C, bool I32OUT, bool RAGGED, bool BIAS, bool ERR = false>
 hipError_t launch_cfg(GemmArgs g, bool may_split, hipStream_t stream) {
     int grid;
-    plan_persistent(g.tiles_m * g.tiles_n, g.K >> 6, may_split, g.dp, g.sk, grid);
+    plan_persistent(g.tiles_m * g.tiles_n * (ERR ? g.err_nc : 1), g.K >> 6, may_split, g.dp, g.sk, grid);
     g.full_grid = full_grid();
     hipLaunchKernelGGL((w4a4_gemm_kernel<C, I32OUT, RAGGED, BIAS, ERR>), dim3((unsigned)grid), dim3(C::NT), 0, stream, g);
     return hipGetLastError();
@@ -1522,9 +1537,9 @@ int64_t gemm_err_partials(int64_t M, int64_t N) {
     return ((M + TCfg::BM - 1) / TCfg::BM) * ((N + TCfg::BN - 1) / TCfg::BN) * TCfg::NW;
 }
 
-hipError_t launch_gemm_err(const uint8_t *Xq, const float *xs, const uint8_t *Wq, const float *ws,
-                           int64_t M, int64_t N, int K, const float *Y0, int64_t ldy0, double *partials,
-                           hipStream_t stream) {
+hipError_t launch_gemm_err(const uint8_t *Xq, const float *xs, const uint8_t *Wq, const float *ws, int nc,
+                           int64_t wq_stride, int64_t ws_stride, int64_t M, int64_t N, int K, const float *Y0,
+                           int64_t ldy0, double *partials, hipStream_t stream) {
     GemmArgs g{};
     g.Xq = Xq;
     g.xs = xs;
@@ -1538,6 +1553,14 @@ hipError_t launch_gemm_err(const uint8_t *Xq, const float *xs, const uint8_t *Wq
     g.y0 = Y0;
     g.ldy0 = ldy0;
     g.errp = partials;
+    // The candidates' tiles of one target tile are neighbours in the tile
+    // order, so they run on one XCD at the same time and its L2 serves the
+    // fp32 target and the activation panel to all of them.
+    g.err_nc = nc;
+    g.err_wq = wq_stride;
+    g.err_ws = ws_stride;
+    g.err_p = gemm_err_partials(M, N);
+    if (nc < 1 || (int64_t)g.tiles_m * g.tiles_n * nc > INT32_MAX) return hipErrorInvalidValue;
     // whole tiles (no workspace): each tile's partials come from its one epilogue
     const bool ragged = N % 16 != 0 || ldy0 % 4 != 0 || reinterpret_cast<uintptr_t>(Y0) % 16 != 0;
     return ragged ? launch_cfg<TCfg, false, true, false, true>(g, false, stream)
