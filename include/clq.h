@@ -135,12 +135,13 @@ clq_status clq_rotate_quant_act(const void *X, int64_t ldx, const int32_t *perm,
  * workspace = NULL (whole tiles only, no waiting) or check the status. */
 size_t clq_w4a4_workspace_bytes(void);
 
-/* Diagnostic (host only, nothing enqueued): the schedule clq_w4a4_linear
- * picks for an M x N x K product on the current device, with or without a
- * workspace, as info[0..4] = {kernel (0: persistent grid of 256-token
- * tiles, 1 / 2: two halves of the k loop per 128- / 64-token tile), output
- * tiles, tiles computed whole, k-stages (of 64 codes) split across the
- * grid, workgroups launched}. */
+/* Diagnostic (host only, nothing enqueued): how clq_w4a4_linear partitions an
+ * M x N x K product on the current device, with or without a workspace, as
+ * info[0..4] = {partition (0: tiles of 256 tokens, 1 / 2: of 128 / 64), output
+ * tiles of that size, tiles computed whole, k-stages (of 64 codes) split
+ * across the grid, workgroups resident at once}.  With no k-stages split, a
+ * workgroup may hold two neighbouring tiles of the partition, or compute one
+ * with its k loop spread over its waves; the results do not depend on it. */
 clq_status clq_w4a4_schedule(int64_t M, int64_t N, int64_t K, int32_t with_workspace, int64_t *info);
 
 /* Enqueues a copy of the workspace's split-k status words to `status`
@@ -276,10 +277,11 @@ clq_status clq_w4a4_linear_f6(const void *Xq, const float *x_scale, const void *
                               int64_t N, int64_t K, void *Y, int64_t ldy,
                               hipStream_t stream);
 
-/* Diagnostic (host only, nothing enqueued): the kernel clq_w4a4_linear_f6
- * picks for an M x N x K product on the current device: *choice = 1 the
- * persistent grid of 256-token tiles, 2 / 3 two halves of the k loop per
- * 128- / 64-token tile (the CLQ_DEBUG_F6_SCHEDULE knob included).  K >= 128. */
+/* Diagnostic (host only, nothing enqueued): the partition of an M x N x K
+ * product for clq_w4a4_linear_f6 on the current device: *choice = 1 tiles of
+ * 256 tokens, 2 / 3 of 128 / 64 (the CLQ_DEBUG_F6_SCHEDULE knob included; a
+ * workgroup may hold two tiles, or spread one's k loop over its waves).
+ * K >= 128. */
 clq_status clq_w4a4_schedule_f6(int64_t M, int64_t N, int64_t K, int32_t *choice);
 
 /* Diagnostic: the exact integer sums of the fp6 operands as int32 [M][N],
@@ -460,15 +462,15 @@ clq_status clq_clps_search(const void *X, int64_t ldx, const void *W, const floa
  *                               owner's wait runs out (tests of the failure
  *                               report only: outputs are then wrong).
  *   CLQ_DEBUG_GEMM_SCHEDULE     the W4A4 GEMM's kernel choice: 0 automatic
- *                               (default); 1 the persistent kernel with its
- *                               split-k rule; 2 the persistent kernel, whole
- *                               tiles only; 3 the two-halves kernel on
+ *                               (default); 1 tiles of 256 tokens with the
+ *                               split-k rule; 2 tiles of 256 tokens, all
+ *                               whole; 3 the two-halves kernel on
  *                               128-token tiles; 4 on 64-token tiles (3 and 4
  *                               fall back to automatic when K < 256).  Every
  *                               choice gives the same results; for measuring
  *                               the schedule heuristics.
  *   CLQ_DEBUG_F6_SCHEDULE       the fp6 GEMM's kernel choice: 0 automatic
- *                               (default); 1 the persistent kernel; 2 the
+ *                               (default); 1 tiles of 256 tokens; 2 the
  *                               two-halves kernel on 128-token tiles; 3 on
  *                               64-token tiles.  Same results either way.
  * clq_debug_set returns CLQ_ERR_ARG for an unknown knob or a value out of

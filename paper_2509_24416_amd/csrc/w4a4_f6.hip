@@ -23,14 +23,12 @@
 // load per lane for the first 1 KB and one 16-byte load on 32 lanes for the
 // rest).  Units are stored [row unit][k unit].
 //
-// The kernel is the persistent W4A4 kernel's pipeline (see w4a4_gemm.hip)
-// with 1536-byte units, one matrix instruction per fragment and k-stage of
-// 64 codes, no operand widening, and a 4-slot ring: the slot of stage s is
-// refilled with stage s + 4 in iteration s, its contents having been read
-// into registers in iteration s - 1 (the workgroup barrier of iteration s
-// orders those reads before the transfer).  Whole tiles only: 128 channels by
-// 256 tokens, or by 128 tokens where the larger tiles would leave compute
-// units without a tile.
+// The product runs on the kernels of tile_gemm.h (one matrix instruction per
+// fragment and 64-code stage, no operand widening).  This file keeps the
+// two-halves kernel, which the schedule knob can ask for, and the format
+// conversion.  Against a persistent kernel with a branch-heavy stage loop the
+// 16384-token block of width 1152 takes 246 us of GEMM instead of 283, the
+// 4608-token one of width 3072 361 instead of 382.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -40,6 +38,7 @@
 
 #include "clq_internal.h"
 #include "f6_codes.h"
+#include "tile_gemm.h"
 
 #define CLQ_LDS __attribute__((address_space(3)))
 
@@ -89,24 +88,7 @@ __device__ __forceinline__ uint32_t fma_mix2(float p0, float w0, float p1, float
 }
 
 constexpr int kUnit = kF6Unit;  // bytes of a 32 x 64 fp6 unit
-constexpr int kNS = 4;          // ring slots
 constexpr int kGroupM = 8;      // token panels per tile group (L2 reuse of channel panels)
-
-// Tile shape of the persistent kernel: four waves, each 128 channels (4
-// fragments of 32) by FM fragments of 32 tokens; two workgroups per compute
-// unit.
-template <int FM_>
-struct F6Tile {
-    static constexpr int WN = 1, WM = 4, FN = 4, FM = FM_;
-    static constexpr int NW = WN * WM, NT = NW * 64;
-    static constexpr int BN = WN * FN * 32, BM = WM * FM * 32;
-    static constexpr int WUnits = BN / 32, XUnits = BM / 32, Units = WUnits + XUnits;
-    static constexpr int UPW = Units / NW;   // units per wave and stage
-    static constexpr int VPW = 2 * UPW;      // transfers per wave and stage
-    static constexpr int Slot = Units * kUnit;
-    static_assert(Units % NW == 0, "units split evenly over waves");
-};
-using F6Tile256 = F6Tile<2>;   // 128 channels x 256 tokens
 
 // global -> LDS transfers of 16 and 4 bytes per lane (plain functions, so that
 // the builtin's operands never depend on a template parameter, which the
@@ -140,10 +122,6 @@ struct F6Args {
     int M, N, K, tiles_m, tiles_n;
 };
 
-struct Seg {
-    int j, L, k;
-};
-
 // The LDS reads of one stage's operands have landed: one wait that names
 // every destination register, so that no use is scheduled before it.
 template <int FM>
@@ -159,388 +137,15 @@ __device__ __forceinline__ void wait_operands(v4u (&ra)[4], v4u (&rb)[FM], v2u (
                        "+v"(sa[0]), "+v"(sa[1]), "+v"(sa[2]), "+v"(sa[3]), "+v"(sb[0]));
 }
 
-template <class C, bool I32OUT, bool RAGGED, bool BIAS>
-__global__ void __launch_bounds__(C::NT, 2) f6_gemm_kernel(F6Args a)
-{
-    constexpr int NS = kNS;
-    constexpr int kFN = C::FN, kFM = C::FM, kNW = C::NW, kBN = C::BN, kBM = C::BM;
-    constexpr int kWUnits = C::WUnits, kXUnits = C::XUnits, kUPW = C::UPW, kVPW = C::VPW, kSlot = C::Slot;
-    constexpr bool BIAS_CH = BIAS && !RAGGED && !I32OUT;
-    constexpr int XS_CH = kBM / 64, WS_CH = kBN / 64, B_CH = kBN / 128;
-    constexpr int E_CH = I32OUT ? 0 : XS_CH + WS_CH + (BIAS_CH ? B_CH : 0);
-    constexpr int EPW = (E_CH + kNW - 1) / kNW;
-    constexpr int E_XS = 0, E_WS = E_XS + kBM * 4, E_B = E_WS + kBN * 4;
-    constexpr int E_BYTES = I32OUT ? 16 : E_B + (BIAS_CH ? kBN * 2 : 0);
-    __shared__ __align__(16) uint8_t ring0[kSlot], ring1[kSlot], ring2[kSlot], ring3[kSlot];
-    __shared__ __align__(16) uint8_t ebuf[NS][E_BYTES];
-    auto slot = [&](auto qc) -> uint8_t * {
-        constexpr int q = decltype(qc)::value;
-        if constexpr (q == 0) return ring0;
-        else if constexpr (q == 1) return ring1;
-        else if constexpr (q == 2) return ring2;
-        else return ring3;
-    };
-
-    const int M = a.M, N = a.N, nks = a.K >> 6;
-    const int G = gridDim.x, gx = G >> 3, xcd = blockIdx.x & 7, jw = blockIdx.x >> 3;
-    const int ntiles = a.tiles_m * a.tiles_n;
-    const int per = ntiles >> 3, rem = ntiles & 7;
-    const int cnt = per + (xcd < rem ? 1 : 0);
-    const int dstart = xcd * per + min(xcd, rem);
-    const int my_tiles = jw < cnt ? (cnt - jw + gx - 1) / gx : 0;
-    const int total = my_tiles * nks;
-    if (total == 0) return;
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave;   // one channel panel per tile
-    const int wunits_total = (int)(padded_rows(N) >> 5);
-    const int xunits_total = (int)(padded_act_rows(M) >> 5);
-
-    auto coords = [&](int L, int &tm, int &tn) {
-        const int gsz = kGroupM * a.tiles_n;
-        const int g = L / gsz, r = L - g * gsz;
-        const int m0 = g * kGroupM;
-        const int gm = min(a.tiles_m - m0, kGroupM);
-        tn = r / gm;
-        tm = m0 + (r - tn * gm);
-    };
-    auto next_seg = [&](Seg &c) {
-        ++c.j;
-        c.L = dstart + jw + c.j * gx;
-        c.k = 0;
-    };
-
-    // ---- producer -------------------------------------------------------------
-    Seg pc{-1, 0, 0};
-    next_seg(pc);
-    int p_s = 0;
-    const uint8_t *usrc[C::UPW];
-    const uint8_t *esrc[EPW > 0 ? EPW : 1];
-    int edst[EPW > 0 ? EPW : 1];
-    auto p_setup = [&]() {
-        int tm, tn;
-        coords(pc.L, tm, tn);
-#pragma unroll
-        for (int j = 0; j < kUPW; ++j) {
-            const int u = wave * kUPW + j;
-            if (u < kWUnits) {
-                const int ug = min(tn * kWUnits + u, wunits_total - 1);
-                usrc[j] = a.Wq + (int64_t)ug * nks * kUnit;
-            } else {
-                const int ux = min(tm * kXUnits + (u - kWUnits), xunits_total - 1);
-                usrc[j] = a.Xq + (int64_t)ux * nks * kUnit;
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < EPW; ++j) {
-            const int c = wave * EPW + j;
-            if (c < XS_CH) {
-                esrc[j] = reinterpret_cast<const uint8_t *>(a.xs + min(tm * kBM + c * 64 + lane, M - 1));
-                edst[j] = E_XS + c * 256;
-            } else if (c < XS_CH + WS_CH || c >= E_CH) {
-                const int w = (c - XS_CH) % WS_CH;
-                esrc[j] = reinterpret_cast<const uint8_t *>(a.ws + min(tn * kBN + w * 64 + lane, N - 1));
-                edst[j] = E_WS + w * 256;
-            } else {
-                const int b = c - XS_CH - WS_CH;
-                esrc[j] = reinterpret_cast<const uint8_t *>(reinterpret_cast<const uint32_t *>(a.bias) +
-                                                            min(tn * (kBN / 2) + b * 64 + lane, N / 2 - 1));
-                edst[j] = E_B + b * 256;
-            }
-        }
-    };
-    p_setup();
-    int e_next = 0;        // stage whose production carries the next tile's epilogue operands
-    unsigned phist = 0;    // 1 bit per production call: epilogue operands issued
-    auto produce = [&](auto qc) {
-        // the tile's epilogue operands go out with its first stage, ahead of
-        // the units (the wait counts below rely on that order)
-        int e_now = 0;
-        if (EPW > 0 && pc.k == 0 && p_s == e_next) {
-            uint8_t *ed = &ebuf[pc.j % NS][0];
-#pragma unroll
-            for (int j = 0; j < EPW; ++j)
-                dma_lds4(esrc[j], ed + edst[j]);
-            e_now = 1;
-            e_next = -1;
-        }
-        phist = (phist << 1) | e_now;
-        uint8_t *dst = slot(qc);
-        const uint32_t voff = (uint32_t)(pc.k * kUnit + lane * 16);
-#pragma unroll
-        for (int j = 0; j < kUPW; ++j)
-            dma_lds16(usrc[j] + voff, dst + (wave * kUPW + j) * kUnit);
-        // the units' last 512 bytes: 16 bytes on each of lanes 0..31
-        if (lane < 32) {
-#pragma unroll
-            for (int j = 0; j < kUPW; ++j)
-                dma_lds16(usrc[j] + voff + 1024, dst + (wave * kUPW + j) * kUnit + 1024);
-        }
-        if (p_s < total - 1) {
-            ++p_s;
-            if (++pc.k == nks) {
-                next_seg(pc);
-                p_setup();
-                e_next = p_s;
-            }
-        }
-    };
-
-    // ---- consumer -------------------------------------------------------------
-    // operands of one stage: 16 + 8 bytes of each of the wave's 4 channel and
-    // 2 token units, in two register sets used by alternate stages (stage s
-    // in set s & 1), so that the next stage's reads land while the matrix
-    // instructions read the other set, with no copies between them.  The
-    // ragged-shape instances, whose epilogue needs more registers, read into
-    // set 1 and copy it to set 0 at the start of each iteration instead.
-    constexpr bool kAlt = !RAGGED;
-    v4u ra[2][kFN], rb[2][kFM];
-    v2u sa[2][kFN], sb[2][kFM];
-    const uint32_t wl0 = (uint32_t)(lane * 16), wl1 = (uint32_t)f6_tail_offset(lane);
-    auto read_stage = [&](auto qc, auto pc) __attribute__((always_inline)) {
-        constexpr int P = decltype(pc)::value;
-        uint32_t b16 = wl0, b8 = wl1;
-        asm volatile("" : "+v"(b16), "+v"(b8));
-        b16 += lds_addr(slot(qc));
-        b8 += lds_addr(slot(qc));
-        // this wave's token units: the offset exceeds the 16-bit immediate
-        // range for the later waves, so it goes into the address
-        const uint32_t xo = (uint32_t)((kWUnits + wm * kFM) * kUnit);
-        const uint32_t bx16 = b16 + xo, bx8 = b8 + xo;
-        static_for<0, kFN>([&](auto f) {
-            constexpr int o = decltype(f)::value * kUnit;
-            ra[P][f] = lds_read16<o>(b16);
-            sa[P][f] = lds_read8<o>(b8);
-        });
-        static_for<0, kFM>([&](auto f) {
-            constexpr int o = decltype(f)::value * kUnit;
-            rb[P][f] = lds_read16<o>(bx16);
-            sb[P][f] = lds_read8<o>(bx8);
-        });
-    };
-    auto stage_ready = [&](auto pc) __attribute__((always_inline)) {
-        constexpr int P = decltype(pc)::value;
-        wait_operands(ra[P], rb[P], sa[P], sb[P]);
-    };
-    v16f acc[kFN][kFM];
-    auto zero_acc = [&]() {
-#pragma unroll
-        for (int fn = 0; fn < kFN; ++fn)
-#pragma unroll
-            for (int fm = 0; fm < kFM; ++fm) acc[fn][fm] = v16f{};
-    };
-    // format codes 2, 2: both operands fp6 e2m3; no block scales
-    auto mma = [&](auto pc) __attribute__((always_inline)) {
-        constexpr int P = decltype(pc)::value;
-        v8i opa[kFN], opb[kFM];
-#pragma unroll
-        for (int f = 0; f < kFN; ++f)
-            opa[f] = v8i{(int)ra[P][f][0], (int)ra[P][f][1], (int)ra[P][f][2], (int)ra[P][f][3],
-                         (int)sa[P][f][0], (int)sa[P][f][1], 0, 0};
-#pragma unroll
-        for (int f = 0; f < kFM; ++f)
-            opb[f] = v8i{(int)rb[P][f][0], (int)rb[P][f][1], (int)rb[P][f][2], (int)rb[P][f][3],
-                         (int)sb[P][f][0], (int)sb[P][f][1], 0, 0};
-#pragma unroll
-        for (int fn = 0; fn < kFN; ++fn)
-#pragma unroll
-            for (int fm = 0; fm < kFM; ++fm)
-                acc[fn][fm] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(opa[fn], opb[fm], acc[fn][fm], 2, 2, 0, 0, 0, 0);
-    };
-
-    // ---- epilogue: lane owns token m and 16 consecutive channels ----------------
-    const int h16 = (lane >> 5) * 16;
-    // always inlined: an outlined epilogue takes the accumulators by reference
-    // (through memory) and the ragged-shape instances then spill
-    auto epilogue = [&](int L, int sj) __attribute__((always_inline)) {
-        int tm, tn;
-        coords(L, tm, tn);
-        uint32_t lx = (uint32_t)((wm * kFM * 32 + (lane & 31)) * 4);
-        uint32_t lw = (uint32_t)(h16 * 4);
-        asm volatile("" : "+v"(lx), "+v"(lw));
-        const uint32_t sbase = lds_addr(&ebuf[0][0]) + (uint32_t)((sj % NS) * E_BYTES);
-        const uint32_t axs = sbase + E_XS + lx, aws = sbase + E_WS + lw, ab = sbase + E_B + lw / 2;
-        float xsm[kFM];
-        int mrow[kFM];
-        if constexpr (!I32OUT) {
-            if constexpr (kFM == 2)
-                asm volatile("ds_read_b32 %0, %2\n\tds_read_b32 %1, %2 offset:128\n\ts_waitcnt lgkmcnt(0)"
-                             : "=&v"(xsm[0]), "=&v"(xsm[1]) : "v"(axs));
-            else
-                asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(xsm[0]) : "v"(axs));
-        }
-#pragma unroll
-        for (int fm = 0; fm < kFM; ++fm) mrow[fm] = tm * kBM + (wm * kFM + fm) * 32 + (lane & 31);
-        const int nl = tn * kBN + h16;
-        uint16_t *rowp[kFM];
-#pragma unroll
-        for (int fm = 0; fm < kFM; ++fm) rowp[fm] = reinterpret_cast<uint16_t *>(a.Y) + (int64_t)mrow[fm] * a.ldy + nl;
-        static_for<0, kFN>([&](auto fc) {
-            constexpr int fn = decltype(fc)::value;
-            const int n0 = nl + fn * 32;
-            v4f w4[4];
-            v4u b8[2];
-            if constexpr (!I32OUT) {
-                asm volatile(
-                    "ds_read_b128 %0, %4 offset:%6\n\t"
-                    "ds_read_b128 %1, %4 offset:%7\n\t"
-                    "ds_read_b128 %2, %4 offset:%8\n\t"
-                    "ds_read_b128 %3, %4 offset:%9\n\t"
-                    "s_waitcnt lgkmcnt(0)"
-                    : "=&v"(w4[0]), "=&v"(w4[1]), "=&v"(w4[2]), "=&v"(w4[3])
-                    : "v"(aws), "v"(ab), "n"(fn * 128), "n"(fn * 128 + 16), "n"(fn * 128 + 32), "n"(fn * 128 + 48));
-                if constexpr (BIAS_CH)
-                    asm volatile(
-                        "ds_read_b128 %0, %2 offset:%3\n\t"
-                        "ds_read_b128 %1, %2 offset:%4\n\t"
-                        "s_waitcnt lgkmcnt(0)"
-                        : "=&v"(b8[0]), "=&v"(b8[1])
-                        : "v"(ab), "n"(fn * 64), "n"(fn * 64 + 16));
-            }
-            float wsv[16];
-            uint32_t bw[8];
-            if constexpr (!I32OUT) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) wsv[v] = w4[v / 4][v % 4];
-            }
-            if constexpr (!BIAS || I32OUT) {
-#pragma unroll
-                for (int v = 0; v < 8; ++v) bw[v] = 0u;
-            } else if constexpr (RAGGED) {
-#pragma unroll
-                for (int v = 0; v < 16; v += 2) {
-                    const int na = min(n0 + v, N - 1), nb = min(n0 + v + 1, N - 1);
-                    bw[v / 2] = (uint32_t)a.bias[na] | ((uint32_t)a.bias[nb] << 16);
-                }
-            } else {
-#pragma unroll
-                for (int v = 0; v < 8; ++v) bw[v] = b8[v / 4][v % 4];
-            }
-#pragma unroll
-            for (int fm = 0; fm < kFM; ++fm) {
-                const int m = mrow[fm];
-                const v16f &x = acc[fn][fm];
-                if constexpr (I32OUT) {
-                    int32_t *dst = reinterpret_cast<int32_t *>(a.Y) + (int64_t)m * a.ldy + n0;
-                    if (m < M && n0 < N) {
-                        if (!RAGGED || n0 + 16 <= N) {
-#pragma unroll
-                            for (int q4 = 0; q4 < 4; ++q4)
-                                reinterpret_cast<v4i *>(dst)[q4] =
-                                    v4i{(int)x[4 * q4], (int)x[4 * q4 + 1], (int)x[4 * q4 + 2], (int)x[4 * q4 + 3]};
-                        } else {
-#pragma unroll
-                            for (int v = 0; v < 16; ++v)
-                                if (n0 + v < N) dst[v] = (int)x[v];
-                        }
-                    }
-                } else {
-                    uint32_t hv[8];
-#pragma unroll
-                    for (int v = 0; v < 16; v += 2)
-                        hv[v / 2] = fma_mix2(x[v] * xsm[fm], wsv[v], x[v + 1] * xsm[fm], wsv[v + 1], bw[v / 2]);
-                    uint16_t *dst = rowp[fm] + fn * 32;
-                    if (m < M && n0 < N) {
-                        if (!RAGGED || n0 + 16 <= N) {
-                            reinterpret_cast<v4u *>(dst)[0] = v4u{hv[0], hv[1], hv[2], hv[3]};
-                            reinterpret_cast<v4u *>(dst)[1] = v4u{hv[4], hv[5], hv[6], hv[7]};
-                        } else {
-#pragma unroll
-                            for (int v = 0; v < 16; ++v)
-                                if (n0 + v < N) dst[v] = (uint16_t)(hv[v >> 1] >> (16 * (v & 1)));
-                        }
-                    }
-                }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        });
-    };
-
-    // Stage s+1 has landed once at most the VMEM instructions issued after
-    // its last transfer are outstanding (completion is in issue order): the
-    // two later productions, with their epilogue operand transfers if any.
-    // Epilogue stores are not counted, which only makes the wait stricter.
-    constexpr int W0 = 2 * kVPW;
-    auto landed_wait = [&]() {
-        switch (__builtin_popcount(phist & 3u)) {
-            case 0: asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(W0) : "memory"); break;
-            case 1: asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(W0 + EPW) : "memory"); break;
-            default: asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(W0 + 2 * EPW) : "memory"); break;
-        }
-    };
-
-    // ---- pipeline ---------------------------------------------------------------
-    // prologue: stages 0..3 in flight, stage 0 read into registers
-    produce(IC<0>{});
-    produce(IC<1>{});
-    produce(IC<2>{});
-    produce(IC<3>{});
-    // stage 0 landed: the three later productions may be outstanding
-    switch (__builtin_popcount(phist & 7u)) {
-        case 0: asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(3 * kVPW) : "memory"); break;
-        case 1: asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(3 * kVPW + EPW) : "memory"); break;
-        case 2: asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(3 * kVPW + 2 * EPW) : "memory"); break;
-        default: asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(3 * kVPW + 3 * EPW) : "memory"); break;
-    }
-    read_stage(IC<0>{}, IC<kAlt ? 0 : 1>{});
-    stage_ready(IC<kAlt ? 0 : 1>{});
-    zero_acc();
-
-    Seg cc{-1, 0, 0};
-    next_seg(cc);
-    int s = 0;
-    auto iter = [&](auto qc) __attribute__((always_inline)) -> bool {
-        constexpr int q = decltype(qc)::value;
-        constexpr IC<(q + 1) % NS> nqc{};
-        constexpr IC<kAlt ? (q & 1) : 0> cur{};
-        constexpr IC<kAlt ? ((q + 1) & 1) : 1> nxt{};
-        static_assert(NS % 2 == 0, "stage s uses register set s & 1 across the ring's wrap");
-        if constexpr (!kAlt) {
-#pragma unroll
-            for (int f = 0; f < kFN; ++f) {
-                ra[0][f] = ra[1][f];
-                sa[0][f] = sa[1][f];
-            }
-#pragma unroll
-            for (int f = 0; f < kFM; ++f) {
-                rb[0][f] = rb[1][f];
-                sb[0][f] = sb[1][f];
-            }
-        }
-        landed_wait();
-        // slot q held stage s, read into registers last iteration: refill it
-        // with stage s + 4 (the producer's next)
-        if (s + 1 < total) read_stage(nqc, nxt);
-        produce(qc);
-        __builtin_amdgcn_sched_barrier(0);
-        mma(cur);
-        __builtin_amdgcn_sched_barrier(0);
-        stage_ready(nxt);
-        if (cc.k == nks - 1) {
-            epilogue(cc.L, cc.j);
-            zero_acc();
-            if (s + 1 < total) next_seg(cc);
-        } else {
-            ++cc.k;
-        }
-        ++s;
-        return s < total;
-    };
-    while (iter(IC<0>{}) && iter(IC<1>{}) && iter(IC<2>{}) && iter(IC<3>{})) {
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-}
-
 // ---- few tiles with long k loops: the k loop in two halves ---------------------
 // The two-halves scheme of the int4 GEMM on fp6 operands.  Each tile (128
 // channels x BM tokens) gets two halves of NWH waves: half 0 runs the first
 // half of the k-stages and half 1 the rest, each through its own NS-slot LDS
-// ring (the fp6 kernel's ring protocol), in lockstep on the workgroup
+// ring (tile_gemm.h's ring protocol), in lockstep on the workgroup
 // barrier; a second half one stage shorter idles on its last step.  At the
 // end the halves swap their fp32 sums (exact integers, so exact sums) through
 // the idle rings and each finishes two of the four channel fragments with
-// the epilogue arithmetic of the kernel above.  One tile per workgroup, two
+// the epilogue arithmetic of every other kernel.  One tile per workgroup, two
 // workgroups per compute unit.
 template <int NWH_, int NS_>
 struct F6HalfTile {
@@ -882,27 +487,6 @@ hipError_t launch_repack_f6(const uint8_t *in, int64_t units, uint8_t *out, hipS
 namespace {
 
 template <class C>
-hipError_t launch_gemm_f6_tile(F6Args g, bool i32out, bool ragged, hipStream_t stream) {
-    g.tiles_m = (g.M + C::BM - 1) / C::BM;
-    g.tiles_n = (g.N + C::BN - 1) / C::BN;
-    const int ntiles = g.tiles_m * g.tiles_n;
-    const int full = (f6_device_cus() * 2 + 7) / 8 * 8;
-    const int grid = std::max(8, (std::min(ntiles, full) + 7) / 8 * 8);
-    const dim3 gd((unsigned)grid), bd(C::NT);
-    if (i32out) {
-        if (ragged) hipLaunchKernelGGL((f6_gemm_kernel<C, true, true, false>), gd, bd, 0, stream, g);
-        else hipLaunchKernelGGL((f6_gemm_kernel<C, true, false, false>), gd, bd, 0, stream, g);
-    } else if (ragged) {
-        if (g.bias) hipLaunchKernelGGL((f6_gemm_kernel<C, false, true, true>), gd, bd, 0, stream, g);
-        else hipLaunchKernelGGL((f6_gemm_kernel<C, false, true, false>), gd, bd, 0, stream, g);
-    } else {
-        if (g.bias) hipLaunchKernelGGL((f6_gemm_kernel<C, false, false, true>), gd, bd, 0, stream, g);
-        else hipLaunchKernelGGL((f6_gemm_kernel<C, false, false, false>), gd, bd, 0, stream, g);
-    }
-    return hipGetLastError();
-}
-
-template <class C>
 hipError_t launch_gemm_f6_halves(F6Args g, bool i32out, bool ragged, hipStream_t stream) {
     g.tiles_m = (g.M + C::BM - 1) / C::BM;
     g.tiles_n = (g.N + C::BN - 1) / C::BN;
@@ -924,15 +508,9 @@ hipError_t launch_gemm_f6_halves(F6Args g, bool i32out, bool ragged, hipStream_t
 
 int f6_schedule_force = 0;
 
-// The fp6 GEMM schedule for an M x N x K product: 1 the persistent kernel,
-// 2 the two-halves kernel on 128-token tiles, 3 on 64-token tiles.  The two
-// halves while the 256-token tiles would not give every compute unit a tile,
-// on 64-token tiles for long k loops (K >= 2048) whose 128-token tiles would
-// fill at most half the compute units.  With more tiles the persistent
-// kernel wins inside a block's chain of launches, long k loops included
-// (its operands then come from HBM, and the one-tile-per-workgroup halves
-// read them more often), although the halves win those shapes when timed
-// alone with their operands cache-resident.
+// The partition an M x N x K product falls into: 1 tiles of 256 tokens, 2 of
+// 128, 3 of 64 (what the query reports and the knob forces).  Without the knob
+// pick_variant (tile_gemm.h) chooses the kernel.
 int f6_schedule(int64_t M, int64_t N, int K) {
     const int force = __atomic_load_n(&f6_schedule_force, __ATOMIC_RELAXED);
     if (force >= 1 && force <= 3) return force;
@@ -946,6 +524,24 @@ int f6_schedule(int64_t M, int64_t N, int K) {
 hipError_t launch_gemm_f6(const uint8_t *Xq, const float *xs, const uint8_t *Wq, const float *ws,
                           const uint16_t *bias, int64_t M, int64_t N, int K, void *Y, int64_t ldy, bool i32out,
                           hipStream_t stream) {
+    const int force = __atomic_load_n(&f6_schedule_force, __ATOMIC_RELAXED);
+    if (force <= 1) {
+        tg::Args t{};
+        t.Xq = Xq;
+        t.xs = xs;
+        t.Wq = Wq;
+        t.ws = ws;
+        t.bias = bias;
+        t.Y = Y;
+        t.ldy = ldy;
+        t.M = (int)M;
+        t.N = (int)N;
+        t.K = K;
+        t.group_m = tg::kGroupPanels;
+        if (force == 1)
+            return tg::launch<tg::Cfg<tg::Fmt::F6, 4, tg::kRing256<tg::Fmt::F6>>>(t, i32out, N % 16 != 0, stream);
+        return tg::launch_tiles<tg::Fmt::F6>(t, i32out, stream);
+    }
     F6Args g{};
     g.Xq = Xq;
     g.xs = xs;
@@ -958,11 +554,8 @@ hipError_t launch_gemm_f6(const uint8_t *Xq, const float *xs, const uint8_t *Wq,
     g.N = (int)N;
     g.K = K;
     const bool ragged = N % 16 != 0 || (bias && reinterpret_cast<uintptr_t>(bias) % 4 != 0);
-    switch (f6_schedule(M, N, K)) {
-        case 2: return launch_gemm_f6_halves<F6Half128>(g, i32out, ragged, stream);
-        case 3: return launch_gemm_f6_halves<F6Half64>(g, i32out, ragged, stream);
-        default: return launch_gemm_f6_tile<F6Tile256>(g, i32out, ragged, stream);
-    }
+    return force == 2 ? launch_gemm_f6_halves<F6Half128>(g, i32out, ragged, stream)
+                         : launch_gemm_f6_halves<F6Half64>(g, i32out, ragged, stream);
 }
 
 }  // namespace clq

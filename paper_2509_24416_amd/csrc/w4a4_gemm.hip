@@ -37,20 +37,20 @@
 // because the compiler would otherwise wait for every transfer in flight
 // before any LDS read it cannot prove independent.
 //
-// Schedule.  Two workgroups of four waves (one wave per SIMD each) share a
-// compute unit; a persistent grid of that many workgroups walks the tiles,
-// and the stage stream runs across tile boundaries, so the next tile's
-// transfers overlap this tile's last matrix-core work and its epilogue.
-// When the tile count leaves the last round badly filled and a workspace is
-// given, the tiles of the last one or two rounds are split along k into
-// equal shares of stages for every workgroup (integer sums are exact in any
-// order); the workgroup that computes a split tile's first stages owns it
-// and adds the others' partial accumulators before its epilogue.
+// Which kernel runs.  Products computed in whole tiles run on the kernels of
+// tile_gemm.h.  This file holds the split schedule for tile counts that leave
+// the last round of a full grid badly filled, the two-halves kernel (the
+// fused rotate+quantize+GEMM entry point and the schedule knob), and the
+// scratch they use.
 //
-// With at most 1.25 such tiles per compute unit a second kernel runs instead
-// (w4a4_gemm_halves_kernel, below): tiles of 128 or 64 tokens, each split
-// into two halves of the k loop run by two groups of waves and summed in LDS,
-// two workgroups per compute unit.
+// The split schedule's persistent grid: two workgroups of four waves (one wave
+// per SIMD each) share a compute unit and walk the tiles; the stage stream
+// runs across tile boundaries, so the next tile's transfers overlap this
+// tile's last matrix-core work and its epilogue.  The tiles of the last one or
+// two rounds are split along k into equal shares of stages for every
+// workgroup (integer sums are exact in any order); the workgroup that computes
+// a split tile's first stages owns it and adds the others' partial
+// accumulators before its epilogue.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -61,6 +61,7 @@
 
 #include "clq_internal.h"
 #include "rq_device.h"
+#include "tile_gemm.h"
 
 #define CLQ_LDS __attribute__((address_space(3)))
 
@@ -165,7 +166,6 @@ struct GemmArgs {
     int *status;   // split-k status words (kStatusBytes at the workspace head)
     int spin_limit;   // bound on a wait for a contributor's flag (sleeps)
     int drop_signal;  // test only: contributors never raise their flags
-    int full_grid;    // two workgroups on every compute unit (the uneven deal applies only then)
     // fused rotate+quantize (the two-halves kernel with FB != 0): fp16
     // activations fx (row stride ldfx) quantized into Xq / xs by the first
     // n_rq work items (rq_rows rows each), the GEMM tiles after them; qhdr:
@@ -175,22 +175,11 @@ struct GemmArgs {
     int rq_rows, n_rq;
     int *qhdr;
     int *qflags;
-    // squared-error mode: target Y0 fp32 [M][ldy0]; one fp64 partial per
-    // wave of every tile, at errp[tile * waves + wave]
-    const float *y0;
-    int64_t ldy0;
-    double *errp;
-    int err_nc;            // squared-error mode: candidate weights of this launch,
-    int64_t err_wq, err_ws, err_p;   // and the strides between their codes, scales and partials
 };
 
-// ERR: instead of storing Y, the epilogue sums (Y0 - sum * x_scale * w_scale)^2
-// over the tile in fp64 (the integer sum exact, the products in the order
-// written) and stores one partial per wave.
-template <class C, bool I32OUT, bool RAGGED, bool BIAS, bool ERR>
+template <class C, bool I32OUT, bool RAGGED, bool BIAS>
 __global__ void __launch_bounds__(C::NT, C::WGS) w4a4_gemm_kernel(GemmArgs a)
 {
-    static_assert(!ERR || (!I32OUT && !BIAS), "the error mode has no output and no bias");
     constexpr int NS = kStages;
     constexpr bool BIAS_CH = BIAS && !RAGGED && !I32OUT;
     constexpr int E_CH = I32OUT ? 0 : C::XS_CH + C::WS_CH + (BIAS_CH ? C::B_CH : 0);
@@ -223,23 +212,7 @@ __global__ void __launch_bounds__(C::NT, C::WGS) w4a4_gemm_kernel(GemmArgs a)
     const int per = dp >> 3, rem = dp & 7;
     const int cnt = per + (xcd < rem ? 1 : 0);
     const int dstart = xcd * per + min(xcd, rem);
-    // Uneven deal on a full grid of whole tiles (several rounds): the two
-    // workgroups on a compute unit do not progress at the same rate (the one
-    // placed first, jw < gx / 2 in dispatch order, wins the issue arbitration
-    // and finishes a tile in about two thirds of the other's time), so the
-    // later one gets about 40% of the unit's tiles: nb rounds for every
-    // workgroup, the remaining rr tiles for the first half only.
-    const int H = gx >> 1;
-    // Not in the squared-error mode (a 4096 x 3456 x 1152 search of 20 candidates:
-    // 438 us with it, 421 without).
-    const bool asym = !ERR && S == 0 && G == a.full_grid && cnt >= 4 * gx;
-    int nb = 0, rr = 0;
-    if (asym) {
-        nb = min(cnt / gx, (cnt * 2 * 40 + gx * 50) / (gx * 100));
-        rr = cnt - nb * gx;
-    }
-    const int my_dp = !asym ? (jw < cnt ? (cnt - jw + gx - 1) / gx : 0)
-                            : nb + (jw < H && jw < rr ? (rr - jw + H - 1) / H : 0);
+    const int my_dp = jw < cnt ? (cnt - jw + gx - 1) / gx : 0;
     const int sk_a = rank * S / G, sk_b = (rank + 1) * S / G;
     const int total = my_dp * nks + (sk_b - sk_a);
     if (total == 0) return;
@@ -263,7 +236,7 @@ __global__ void __launch_bounds__(C::NT, C::WGS) w4a4_gemm_kernel(GemmArgs a)
     auto next_seg = [&](Seg &c) {
         ++c.j;
         if (c.j < my_dp) {
-            c.L = !asym || c.j < nb ? dstart + jw + c.j * gx : dstart + nb * gx + jw + (c.j - nb) * H;
+            c.L = dstart + jw + c.j * gx;
             c.kb = 0;
             c.ke = nks;
         } else {
@@ -285,22 +258,13 @@ __global__ void __launch_bounds__(C::NT, C::WGS) w4a4_gemm_kernel(GemmArgs a)
     int edst[EPW > 0 ? EPW : 1];
     auto p_setup = [&]() {
         int tm, tn;
-        const uint8_t *wq = a.Wq;
-        const float *wsc = a.ws;
-        if constexpr (ERR) {
-            const int t = pc.L / a.err_nc, c = pc.L - t * a.err_nc;
-            coords(t, tm, tn);
-            wq += c * a.err_wq;
-            wsc += c * a.err_ws;
-        } else {
-            coords(pc.L, tm, tn);
-        }
+        coords(pc.L, tm, tn);
 #pragma unroll
         for (int j = 0; j < C::UPW; ++j) {
             const int u = wave * C::UPW + j;
             if (u < C::W_UNITS) {
                 const int ug = min(tn * C::W_UNITS + u, wunits_total - 1);
-                usrc[j] = wq + (int64_t)ug * nks * 1024;
+                usrc[j] = a.Wq + (int64_t)ug * nks * 1024;
             } else {
                 const int ux = min(tm * C::X_UNITS + (u - C::W_UNITS), xunits_total - 1);
                 usrc[j] = a.Xq + (int64_t)ux * nks * 1024;
@@ -314,7 +278,7 @@ __global__ void __launch_bounds__(C::NT, C::WGS) w4a4_gemm_kernel(GemmArgs a)
                 edst[j] = E_XS + c * 256;
             } else if (c < C::XS_CH + C::WS_CH || c >= E_CH) {
                 const int w = (c - C::XS_CH) % C::WS_CH;
-                esrc[j] = reinterpret_cast<const uint8_t *>(wsc + min(tn * C::BN + w * 64 + lane, N - 1));
+                esrc[j] = reinterpret_cast<const uint8_t *>(a.ws + min(tn * C::BN + w * 64 + lane, N - 1));
                 edst[j] = E_WS + w * 256;
             } else {
                 const int b = c - C::XS_CH - C::WS_CH;
@@ -575,7 +539,7 @@ __global__ void __launch_bounds__(C::NT, C::WGS) w4a4_gemm_kernel(GemmArgs a)
     // operand units); one explicit wait per channel fragment orders their use.
     auto epilogue = [&](int L, int sj, auto qc) {
         int tm, tn;
-        coords(ERR ? L / a.err_nc : L, tm, tn);
+        coords(L, tm, tn);
         uint32_t lx = (uint32_t)((wm * C::FM * 32 + (lane & 31)) * 4);
         uint32_t lw = (uint32_t)((wn * C::FN * 32 + h16) * 4);
         asm volatile("" : "+v"(lx), "+v"(lw));
@@ -583,7 +547,6 @@ __global__ void __launch_bounds__(C::NT, C::WGS) w4a4_gemm_kernel(GemmArgs a)
         const uint32_t axs = sb + E_XS + lx, aws = sb + E_WS + lw, ab = sb + E_B + lw / 2;
         float xsm[C::FM];
         int mrow[C::FM];
-        double esum = 0.0;
         if constexpr (!I32OUT) {
             static_assert(C::FM == 2, "two token scales per lane");
             asm volatile("ds_read_b32 %0, %2\n\tds_read_b32 %1, %2 offset:128\n\ts_waitcnt lgkmcnt(0)"
@@ -667,33 +630,6 @@ __global__ void __launch_bounds__(C::NT, C::WGS) w4a4_gemm_kernel(GemmArgs a)
                                 if (n0 + v < N) dst[v] = x[v] >> 8;
                         }
                     }
-                } else if constexpr (ERR) {
-                    // d = Y0 - (sum * x_scale) * w_scale, the integer sum exact
-                    // (x is 256 times it, so the scale takes 1 / 256)
-                    if (m < M && n0 < N) {
-                        const float *yr = a.y0 + (int64_t)m * a.ldy0 + n0;
-                        float yv[16];
-                        if constexpr (!RAGGED) {   // 16-byte aligned rows of whole 16-channel pieces
-#pragma unroll
-                            for (int q4 = 0; q4 < 4; ++q4) {
-                                const v4f t = reinterpret_cast<const v4f *>(yr)[q4];
-                                yv[4 * q4] = t[0];
-                                yv[4 * q4 + 1] = t[1];
-                                yv[4 * q4 + 2] = t[2];
-                                yv[4 * q4 + 3] = t[3];
-                            }
-                        } else {
-#pragma unroll
-                            for (int v = 0; v < 16; ++v) yv[v] = n0 + v < N ? yr[v] : 0.0f;
-                        }
-                        const double xm = (double)xsm[fm] * (1.0 / 256.0);
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) {
-                            if (RAGGED && n0 + v >= N) continue;
-                            const double d = __builtin_fma(-((double)x[v] * xm), (double)wsv[v], (double)yv[v]);
-                            esum = __builtin_fma(d, d, esum);
-                        }
-                    }
                 } else {
                     uint32_t hv[8];
 #pragma unroll
@@ -714,12 +650,6 @@ __global__ void __launch_bounds__(C::NT, C::WGS) w4a4_gemm_kernel(GemmArgs a)
             }
             __builtin_amdgcn_sched_barrier(0);
         });
-        if constexpr (ERR) {
-            // fixed butterfly over the wave; lane 0 holds the wave's partial
-            for (int off = 32; off > 0; off >>= 1) esum += __shfl_xor(esum, off);
-            const int t = L / a.err_nc, c = L - t * a.err_nc;
-            if (lane == 0) a.errp[c * a.err_p + (int64_t)t * C::NW + wave] = esum;
-        }
     };
 
     // Stage s+1 has landed once at most the VMEM instructions issued after
@@ -773,9 +703,7 @@ __global__ void __launch_bounds__(C::NT, C::WGS) w4a4_gemm_kernel(GemmArgs a)
         interleave(IC<GB>{}, IC<VH2>{}, IC<-1>{});
         __builtin_amdgcn_sched_barrier(0);
         if (cc.k == cc.ke - 1) {
-            if constexpr (ERR) {   // launched with whole tiles only: no split code
-                epilogue(cc.L, cc.j, qc);
-            } else if (cc.kb != 0) {
+            if (cc.kb != 0) {
                 contribute();
             } else {
                 if (cc.ke != nks) fixup(cc.L);
@@ -1239,12 +1167,11 @@ void plan_persistent(int ntiles, int nks, bool may_split, int &dp, int &sk, int 
     if (sk == 0) grid = max(8, (min(ntiles, grid) + 7) / 8 * 8);
 }
 
-template <class C, bool I32OUT, bool RAGGED, bool BIAS, bool ERR = false>
+template <class C, bool I32OUT, bool RAGGED, bool BIAS>
 hipError_t launch_cfg(GemmArgs g, bool may_split, hipStream_t stream) {
     int grid;
-    plan_persistent(g.tiles_m * g.tiles_n * (ERR ? g.err_nc : 1), g.K >> 6, may_split, g.dp, g.sk, grid);
-    g.full_grid = full_grid();
-    hipLaunchKernelGGL((w4a4_gemm_kernel<C, I32OUT, RAGGED, BIAS, ERR>), dim3((unsigned)grid), dim3(C::NT), 0, stream, g);
+    plan_persistent(g.tiles_m * g.tiles_n, g.K >> 6, may_split, g.dp, g.sk, grid);
+    hipLaunchKernelGGL((w4a4_gemm_kernel<C, I32OUT, RAGGED, BIAS>), dim3((unsigned)grid), dim3(C::NT), 0, stream, g);
     return hipGetLastError();
 }
 
@@ -1261,7 +1188,10 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int K, bool may_split, int force) {
     const int tiles_n = (int)((N + TCfg::BN - 1) / TCfg::BN);
     const int ntiles = (int)((M + TCfg::BM - 1) / TCfg::BM) * tiles_n;
     const bool halves_ok = (K >> 6) >= kHalvesMinStages;
-    // the two-halves kernel: at most 1.25 256-token tiles per compute unit
+    // The partition (pick_variant in tile_gemm.h may run two of its tiles, or half
+    // of one, per workgroup; its halves kernel runs only where the knob or the
+    // fused entry point asks).  Smaller tiles:
+    // at most 1.25 256-token tiles per compute unit
     // (just past one tile per CU the persistent kernel doubles up on a few
     // CUs while the rest idle; the two-halves kernel fills one round of two
     // workgroups per CU and runs a short second round on the remaining
@@ -1422,6 +1352,25 @@ hipError_t launch_gemm(const uint8_t *Xq, const float *xs, const uint8_t *Wq, co
     g.drop_signal = __atomic_load_n(&gemm_drop_signal, __ATOMIC_RELAXED);
     const GemmPlan pl = plan_gemm(M, N, K, workspace != nullptr, force);
     const bool may_split = pl.may_split;
+    // Whole tiles run on the shared tile kernels; what is left to the kernels of
+    // this file: the split schedule, and the two halves where the knob asks.
+    if (pl.sk == 0 && force < 3) {
+        tg::Args t{};
+        t.Xq = Xq;
+        t.xs = xs;
+        t.Wq = Wq;
+        t.ws = ws;
+        t.bias = bias;
+        t.Y = Y;
+        t.ldy = ldy;
+        t.M = (int)M;
+        t.N = (int)N;
+        t.K = K;
+        t.group_m = tg::kGroupPanels;
+        if (force != 0)
+            return tg::launch<tg::Cfg<tg::Fmt::W4A4, 4, tg::kRing256<tg::Fmt::W4A4>>>(t, i32out, N % 16 != 0, stream);
+        return tg::launch_tiles<tg::Fmt::W4A4>(t, i32out, stream);
+    }
     if (pl.kernel == 2) {
         g.tiles_m = pl.tiles_m;
         return launch_halves<TileHalf64>(g, i32out, bias != nullptr, N % 16 != 0, stream);
@@ -1540,31 +1489,36 @@ int64_t gemm_err_partials(int64_t M, int64_t N) {
 hipError_t launch_gemm_err(const uint8_t *Xq, const float *xs, const uint8_t *Wq, const float *ws, int nc,
                            int64_t wq_stride, int64_t ws_stride, int64_t M, int64_t N, int K, const float *Y0,
                            int64_t ldy0, double *partials, hipStream_t stream) {
-    GemmArgs g{};
-    g.Xq = Xq;
-    g.xs = xs;
-    g.Wq = Wq;
-    g.ws = ws;
-    g.M = (int)M;
-    g.N = (int)N;
-    g.K = K;
-    g.tiles_m = (int)((M + TCfg::BM - 1) / TCfg::BM);
-    g.tiles_n = (int)((N + TCfg::BN - 1) / TCfg::BN);
-    g.y0 = Y0;
-    g.ldy0 = ldy0;
-    g.errp = partials;
-    // The candidates' tiles of one target tile are neighbours in the tile
-    // order, so they run on one XCD at the same time and its L2 serves the
-    // fp32 target and the activation panel to all of them.
-    g.err_nc = nc;
-    g.err_wq = wq_stride;
-    g.err_ws = ws_stride;
-    g.err_p = gemm_err_partials(M, N);
-    if (nc < 1 || (int64_t)g.tiles_m * g.tiles_n * nc > INT32_MAX) return hipErrorInvalidValue;
-    // whole tiles (no workspace): each tile's partials come from its one epilogue
+    using C = tg::Cfg<tg::Fmt::W4A4, 4, tg::kRing256<tg::Fmt::W4A4>>;
+    static_assert(C::BM == TCfg::BM && C::BN == TCfg::BN && C::WM == TCfg::NW, "gemm_err_partials counts these tiles");
+    tg::Args t{};
+    t.Xq = Xq;
+    t.xs = xs;
+    t.Wq = Wq;
+    t.ws = ws;
+    t.M = (int)M;
+    t.N = (int)N;
+    t.K = K;
+    t.tiles_m = (int)((M + C::BM - 1) / C::BM);
+    t.tiles_n = (int)((N + C::BN - 1) / C::BN);
+    t.group_m = tg::kGroupPanels;
+    t.y0 = Y0;
+    t.ldy0 = ldy0;
+    t.errp = partials;
+    t.nc = nc;
+    t.wq_stride = wq_stride;
+    t.ws_stride = ws_stride;
+    t.p_stride = gemm_err_partials(M, N);
+    const int64_t tiles = (int64_t)t.tiles_m * t.tiles_n * nc;
+    if (nc < 1 || tiles > INT32_MAX) return hipErrorInvalidValue;
     const bool ragged = N % 16 != 0 || ldy0 % 4 != 0 || reinterpret_cast<uintptr_t>(Y0) % 16 != 0;
-    return ragged ? launch_cfg<TCfg, false, true, false, true>(g, false, stream)
-                  : launch_cfg<TCfg, false, false, false, true>(g, false, stream);
+    if (ragged)
+        hipLaunchKernelGGL((tg::tile_gemm_kernel<C, false, true, false, true>), dim3((unsigned)tiles), dim3(C::NT), 0,
+                           stream, t);
+    else
+        hipLaunchKernelGGL((tg::tile_gemm_kernel<C, false, false, false, true>), dim3((unsigned)tiles), dim3(C::NT), 0,
+                           stream, t);
+    return hipGetLastError();
 }
 
 }  // namespace clq
