@@ -818,10 +818,20 @@ hipError_t launch(Args a, bool i32out, bool ragged, hipStream_t stream) {
 //                           4096 x 3072 -> 3072: 37.5 / 38.8);
 //   t > 6 c                 256-token tiles, which move the fewest operand bytes
 //                           (43200 x 1152 block: 590 us of GEMM against 690).
-// Splits need a stage for every wave.
+// Splits need a stage for every wave.  fp6 operands are half again as large,
+// the matrix work half: four waves only pay up to t = c (2048 x 1152 -> 1152, t =
+// 288: 9.1 over two waves, 10.1 over four; 1536, t = 216: 7.3 both), two up to 2 c,
+// and to 3 c on k loops under 48 stages (1280 x 1152 -> 3456: 11.9, 256-token tiles
+// 12.3; but 1536 x 3072 -> 3072: 21.2 / 20.1).
 enum Variant { kTile256, kTile128, kSplit4, kSplit2 };
+template <Fmt F>
 inline Variant pick_variant(int64_t M, int64_t N, int64_t K, int cus) {
     const int64_t t = (M + 63) / 64 * ((N + 127) / 128), c = cus, nks = K >> 6;
+    if constexpr (F == Fmt::F6) {
+        if (nks >= 4 && t <= c) return kSplit4;
+        if (nks >= 2 && (t <= 2 * c || (t <= 3 * c && nks < 48))) return kSplit2;
+        return t > 4 * c && t <= 6 * c ? kTile128 : kTile256;
+    }
     if (nks >= 4 && (t <= 2 * c || (nks >= 48 && t <= 5 * c && !(t > 3 * c && t <= 4 * c)))) return kSplit4;
     if (nks >= 2 && t <= 3 * c) return kSplit2;
     if (t > 4 * c && t <= 6 * c) return kTile128;
@@ -847,7 +857,7 @@ template <Fmt F> constexpr int kRing128 = F == Fmt::W4A4 ? 4 : 3;
 template <Fmt F>
 hipError_t launch_tiles(const Args &a, bool i32out, hipStream_t stream) {
     const bool ragged = a.N % 16 != 0;
-    switch (pick_variant(a.M, a.N, a.K, compute_units())) {
+    switch (pick_variant<F>(a.M, a.N, a.K, compute_units())) {
         case kTile128: return launch<Cfg<F, 2, kRing128<F>>>(a, i32out, ragged, stream);
         case kSplit4:
             return launch_split<SplitCfg<F, 4>>(a, i32out, ragged, stream);

@@ -25,7 +25,7 @@
 //
 // The product runs on the kernels of tile_gemm.h (one matrix instruction per
 // fragment and 64-code stage, no operand widening).  This file keeps the
-// two-halves kernel, which the schedule knob can ask for, and the format
+// two-halves kernel, for long k loops with few tiles, and the format
 // conversion.  Against a persistent kernel with a branch-heavy stage loop the
 // 16384-token block of width 1152 takes 246 us of GEMM instead of 283, the
 // 4608-token one of width 3072 361 instead of 382.
@@ -525,7 +525,13 @@ hipError_t launch_gemm_f6(const uint8_t *Xq, const float *xs, const uint8_t *Wq,
                           const uint16_t *bias, int64_t M, int64_t N, int K, void *Y, int64_t ldy, bool i32out,
                           hipStream_t stream) {
     const int force = __atomic_load_n(&f6_schedule_force, __ATOMIC_RELAXED);
-    if (force <= 1) {
+    // Long k loops (48 stages or more) with more than one and at most two 128 x
+    // 64 wave tiles per compute unit stay on the two halves, whose four waves
+    // share the operands through LDS (2048 x 4608 -> 1152: 18.8 us, 19.4 with the
+    // k loop over two waves, 20.6 over four, 25.2 on 256-token tiles).
+    const int64_t waves = (M + 63) / 64 * ((N + 127) / 128), cus = tg::compute_units();
+    const bool halves = force == 0 && (K >> 6) >= 48 && waves > cus && waves <= 2 * cus;
+    if (force <= 1 && !halves) {
         tg::Args t{};
         t.Xq = Xq;
         t.xs = xs;
@@ -554,7 +560,7 @@ hipError_t launch_gemm_f6(const uint8_t *Xq, const float *xs, const uint8_t *Wq,
     g.N = (int)N;
     g.K = K;
     const bool ragged = N % 16 != 0 || (bias && reinterpret_cast<uintptr_t>(bias) % 4 != 0);
-    return force == 2 ? launch_gemm_f6_halves<F6Half128>(g, i32out, ragged, stream)
+    return force == 2 || halves ? launch_gemm_f6_halves<F6Half128>(g, i32out, ragged, stream)
                          : launch_gemm_f6_halves<F6Half64>(g, i32out, ragged, stream);
 }
 

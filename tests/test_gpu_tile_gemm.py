@@ -3,8 +3,10 @@
 The kernel follows from t, the 128 x 64 wave tiles of the product (256 compute
 units assumed): the k loop over four waves up to t = 512 (and to 1280 on k
 loops of 48 stages of 64 codes or more), over two up to 768, tiles of 256
-tokens up to 1024, of 128 up to 1536, of 256 beyond; fewer stages than waves
-fall through to the next choice.  Shapes sit on both sides of each line, with
+tokens up to 1024, of 128 up to 1536, of 256 beyond; fp6 codes take four waves
+to 256, two to 512 (768 under 48 stages), and two halves of a workgroup from 256
+to 512 on longer k loops; fewer stages than waves fall through to the next
+choice.  Shapes sit on both sides of each line, with
 ragged token and channel counts and stage counts that leave remainders, for
 every code storage.  Sums are integers and exact.  An fp16 output is one
 rounding of fma(p, w_scale, bias), p the fp32 rounding of sum * x_scale:
@@ -29,7 +31,7 @@ def clq():
 
 SHAPES = [(1, 16, 128), (33, 130, 128), (65, 200, 192), (300, 1000, 256), (257, 1009, 448), (2000, 2040, 320),
           (2100, 2048, 256), (1500, 4000, 192), (2120, 3072, 320), (4000, 2050, 128), (2040, 3968, 3072),
-          (2100, 4090, 192), (2560, 3072, 3136), (6200, 2000, 256), (6208, 2050, 128)]
+          (1100, 3072, 256), (1100, 3000, 3072), (2100, 4090, 192), (2560, 3072, 3136), (6200, 2000, 256), (6208, 2050, 128)]
 
 
 def _codes(clq, fmt, x, w, M, N, K, block):
