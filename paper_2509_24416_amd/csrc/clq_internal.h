@@ -74,7 +74,7 @@ __host__ __device__ inline int64_t q8_piece_offset(int64_t u, int rho, int64_t c
 // bits: 4 (packed int4 layouts above), 6 (the 4-bit grid in the fp6 layout
 // of f6_codes.h) or 8 (int8 layout).  alpha_dev, when
 // given, holds the weights' clip ratio in device memory (alpha is then unused).
-// batch > 1 (weights with alpha_dev only): batch quantizations of the same
+// batch > 1 (4-bit weights with alpha_dev only): batch quantizations of the same
 // rows, quantization y with clip ratio alpha_dev[y] into out + y * out_stride
 // and scale + y * scale_stride.
 hipError_t launch_rotate_quant(const uint16_t *X, int64_t ldx, const int32_t *perm,

@@ -168,10 +168,10 @@ __device__ __forceinline__ void store_codes(const float (&x)[4][8], const float 
 }
 
 // NCH: chunks per lane, held in registers from the rotation to the codes (1:
-// rows of up to 8192 columns, 2: up to 16384); 0: any width, the rotation done
-// twice, once for the row maxima and once for the codes.
+// rows of up to 8192 columns, 2: up to 16384).  With one chunk the registers
+// are held to 72, for 28 waves a compute unit.
 template <int B, int QB, bool WEIGHT, int NCH>
-__global__ void __launch_bounds__(kMaxLanes)
+__global__ void __launch_bounds__(kMaxLanes) __attribute__((amdgpu_waves_per_eu(NCH == 1 ? 7 : 4)))
 rotate_quant_kernel(RqArgs a)
 {
     extern __shared__ __align__(16) uint2 gat[];   // gathered inputs: [group][K] columns of four rows
@@ -231,30 +231,18 @@ rotate_quant_kernel(RqArgs a)
 #pragma unroll
         for (int e = 0; e < 8; e += 2) {
             const int k0 = p[e], k1 = p[e + 1];
-            if constexpr (NCH != 0) {
-                const uint2 q0 = grow[k0], q1 = grow[k1];
-                stage1_pair(q0.x, q1.x, x[0][e], x[0][e + 1]);
-                stage1_pair_hi(q0.x, q1.x, x[1][e], x[1][e + 1]);
-                stage1_pair(q0.y, q1.y, x[2][e], x[2][e + 1]);
-                stage1_pair_hi(q0.y, q1.y, x[3][e], x[3][e + 1]);
-            } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    uint32_t h0 = 0u, h1 = 0u;
-                    if (rv[r] && chunk < cpr) {
-                        h0 = xr[r][k0];
-                        h1 = xr[r][k1];
-                    }
-                    stage1_pair(h0, h1, x[r][e], x[r][e + 1]);
-                }
-            }
+            const uint2 q0 = grow[k0], q1 = grow[k1];
+            stage1_pair(q0.x, q1.x, x[0][e], x[0][e + 1]);
+            stage1_pair_hi(q0.x, q1.x, x[1][e], x[1][e + 1]);
+            stage1_pair(q0.y, q1.y, x[2][e], x[2][e + 1]);
+            stage1_pair_hi(q0.y, q1.y, x[3][e], x[3][e + 1]);
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) fwht8_rest(x[r]);
         cross_stages<B, 4>(x, cs);
     };
 
-    constexpr int NX = NCH == 0 ? 1 : NCH;
+    constexpr int NX = NCH;
     float x[NX][4][8];
     float m[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     auto take_max = [&](const float (&y)[4][8]) {
@@ -263,50 +251,36 @@ rotate_quant_kernel(RqArgs a)
 #pragma unroll
             for (int e = 0; e < 8; e += 2) m[r] = fmaxf(fmaxf(m[r], fabsf(y[r][e])), fabsf(y[r][e + 1]));
     };
-    if constexpr (NCH != 0) {
-        uint4 v[NX][4];
+    uint4 v[NX][4];
 #pragma unroll
-        for (int i = 0; i < NX; ++i) load(lane_c + i * a.stride, v[i]);
-        if (gather) {
-            // columns k of the group's four rows side by side: one 8-byte read
-            // per gathered column serves all four
+    for (int i = 0; i < NX; ++i) load(lane_c + i * a.stride, v[i]);
+    if (gather) {
+        // columns k of the group's four rows side by side: one 8-byte read
+        // per gathered column serves all four
 #pragma unroll
-            for (int i = 0; i < NX; ++i) {
-                const int chunk = lane_c + i * a.stride;
-                uint32_t q[16];
-                interleave_rows(v[i], q);
-                if (glive && chunk < cpr) {
-                    uint4 *dst = reinterpret_cast<uint4 *>(gat + gl * a.K + chunk * 8);
+        for (int i = 0; i < NX; ++i) {
+            const int chunk = lane_c + i * a.stride;
+            uint32_t q[16];
+            interleave_rows(v[i], q);
+            if (glive && chunk < cpr) {
+                uint4 *dst = reinterpret_cast<uint4 *>(gat + gl * a.K + chunk * 8);
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) dst[j] = make_uint4(q[4 * j], q[4 * j + 1], q[4 * j + 2], q[4 * j + 3]);
-                }
+                for (int j = 0; j < 4; ++j) dst[j] = make_uint4(q[4 * j], q[4 * j + 1], q[4 * j + 2], q[4 * j + 3]);
             }
-            __syncthreads();   // also orders the clear of rowmax
-            // (an octet past the row's end works on other columns, and is
-            // left out of the maximum and the codes)
-#pragma unroll
-            for (int i = 0; i < NX; ++i) rotate_gathered(lane_c + i * a.stride, x[i]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < NX; ++i) rotate(v[i], x[i]);
-            __syncthreads();   // rowmax cleared
         }
+        __syncthreads();   // also orders the clear of rowmax
+        // (an octet past the row's end works on other columns, and is
+        // left out of the maximum and the codes)
 #pragma unroll
-        for (int i = 0; i < NX; ++i)
-            if (lane_c + i * a.stride < cpr) take_max(x[i]);
+        for (int i = 0; i < NX; ++i) rotate_gathered(lane_c + i * a.stride, x[i]);
     } else {
-        __syncthreads();
-        for (int base = 0; base < cpr; base += a.stride) {
-            if (gather) {
-                rotate_gathered(lane_c + base, x[0]);
-            } else {
-                uint4 v[4];
-                load(lane_c + base, v);
-                rotate(v, x[0]);
-            }
-            take_max(x[0]);
-        }
+#pragma unroll
+        for (int i = 0; i < NX; ++i) rotate(v[i], x[i]);
+        __syncthreads();   // rowmax cleared
     }
+#pragma unroll
+    for (int i = 0; i < NX; ++i)
+        if (lane_c + i * a.stride < cpr) take_max(x[i]);
 
     // row maxima: over the octet, then lane k < 4 of it reports row k
     octet_max(m);
@@ -317,7 +291,10 @@ rotate_quant_kernel(RqArgs a)
 
     const int prow = t & 3;   // the row this lane divides for
     const float am = glive ? __uint_as_float(rowmax[gl * 4 + prow]) : 0.0f;
-    for (int y = 0; y < a.batch; ++y) {
+    // (several quantizations of the same rows: 4-bit weights only, so that the
+    // others need not keep the rotated values past their codes)
+    const int batch = WEIGHT && QB == 4 ? a.batch : 1;
+    for (int y = 0; y < batch; ++y) {
         const float al = a.alpha_dev != nullptr ? a.alpha_dev[y] : a.alpha;
         const float ac = WEIGHT ? al * am : am;
         const float rc = (ac == 0.0f) ? 0.0f : Grid<QB>::qmax / ac;
@@ -329,39 +306,236 @@ rotate_quant_kernel(RqArgs a)
         rs[2] = lane_xchg<kQuadLane2>(rc) * cs.sign;
         rs[3] = lane_xchg<kQuadLane3>(rc) * cs.sign;
         uint8_t *out = a.out + y * a.out_stride;
-        if constexpr (NCH != 0) {
 #pragma unroll
-            for (int i = 0; i < NX; ++i) {
-                const int chunk = lane_c + i * a.stride;
-                store_codes<QB, WEIGHT>(x[i], rs, u, 4 * s, chunk, a.K, out, glive && chunk < cpr);
+        for (int i = 0; i < NX; ++i) {
+            const int chunk = lane_c + i * a.stride;
+            store_codes<QB, WEIGHT>(x[i], rs, u, 4 * s, chunk, a.K, out, glive && chunk < cpr);
+        }
+    }
+}
+
+// ---- rows of more than 16384 columns ---------------------------------------------
+// Four such rows do not fit a workgroup's registers.  One workgroup per row: the
+// row staged in LDS with coalesced 16-byte loads (each chunk of a Hadamard
+// block in an XOR-swizzled slot, so that the block reads hit distinct banks),
+// then one block per lane in registers.  Rotating twice with the kernel above
+// instead took 17 us for 64 x 32768 against 7, and gathering its inputs from
+// memory 115 against 10.
+// (Lanes per workgroup never exceed 512 for b >= 64, which lets the compiler
+// keep a 128-element block in registers.)
+// Sixteen quantized words (code + 128 in bits 0..7, bits 8..21 clear) into
+// one 16-byte int8 operand piece: codes 0, 2, ..., 14 in bytes 0..7, codes 1,
+// 3, ..., 15 in bytes 8..15 (the order of the widened 4-bit operands), two's
+// complement.
+__device__ __forceinline__ uint4 pack16_q8(const uint32_t *w) {
+    auto four = [](uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+        const uint32_t ab = __builtin_amdgcn_perm(b, a, 0x0c0c0400u);
+        const uint32_t cd = __builtin_amdgcn_perm(d, c, 0x0c0c0400u);
+        return __builtin_amdgcn_perm(cd, ab, 0x05040100u) ^ 0x80808080u;
+    };
+    return make_uint4(four(w[0], w[2], w[4], w[6]), four(w[8], w[10], w[12], w[14]),
+                      four(w[1], w[3], w[5], w[7]), four(w[9], w[11], w[13], w[15]));
+}
+
+// The int8 codes of one lane's b-element block (codes 32c .. of the row's
+// 32-code chunks j * b/32 + c): two 16-byte operand pieces per chunk.
+template <int B, bool WEIGHT>
+__device__ __forceinline__ void store_q8(const float *x, float rc, int64_t grow, int j, int K,
+                                         uint8_t *__restrict__ out) {
+    constexpr float M = Grid<8>::magic, Q = Grid<8>::qmax;
+    const int64_t u = grow >> 5;
+    const int rho = WEIGHT ? wq_rho((int)(grow & 31)) : (int)(grow & 31);
+#pragma unroll
+    for (int c = 0; c < B / 32; ++c) {
+        const int64_t c32 = (int64_t)j * (B / 32) + c;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            uint32_t w[16];
+#pragma unroll
+            for (int t = 0; t < 16; ++t) {
+                float v = __builtin_fmaf(x[32 * c + 16 * q + t], rc, M);
+                if constexpr (WEIGHT) v = __builtin_amdgcn_fmed3f(v, M - Q, M + Q);
+                w[t] = __float_as_uint(v);
+            }
+            *reinterpret_cast<uint4 *>(out + q8_piece_offset(u, rho, c32, q, K)) = pack16_q8(w);
+        }
+    }
+}
+
+template <int B>
+constexpr int wide_max_threads() { return B == 32 ? 1024 : 512; }
+
+template <int B, bool WEIGHT, int QB>
+__global__ void __launch_bounds__(wide_max_threads<B>())
+rotate_quant_wide_kernel(const uint16_t *__restrict__ X, int64_t ldx,
+                    const int32_t *__restrict__ perm, int64_t rows_valid,
+                    int64_t rows_alloc, int K, int R, float alpha, const float *__restrict__ alpha_dev,
+                    float post_scale, uint8_t *__restrict__ out, float *__restrict__ scale_out,
+                    int64_t out_stride, int64_t scale_stride)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    // blockIdx.y selects one of several quantizations of the same rows
+    // (clip ratio alpha_dev[y], outputs at y * stride)
+    out += (int64_t)blockIdx.y * out_stride;
+    scale_out += (int64_t)blockIdx.y * scale_stride;
+    if (alpha_dev != nullptr) alpha_dev += blockIdx.y;
+    constexpr int CPB = B / 8;            // 16-byte chunks per block
+    const int cpr = K >> 3;               // chunks per row
+    const int nb = K / B;                 // blocks per row
+    uint4 *tile = reinterpret_cast<uint4 *>(smem);
+    unsigned *rowmax = reinterpret_cast<unsigned *>(smem + (size_t)R * K * 2);
+
+    const int t = threadIdx.x;
+    const int T = blockDim.x;
+    const int64_t row0 = (int64_t)blockIdx.x * R;
+    const int rows = (int)min((int64_t)R, rows_alloc - row0);
+
+    if (t < R) rowmax[t] = 0u;
+
+    // 1. coalesced copy of the rows into LDS (rows past rows_valid are zeros)
+    {
+        int r = t / cpr, cc = t - r * cpr;
+        const int dr = T / cpr, dc = T - dr * cpr;
+        while (r < rows) {
+            uint4 v = make_uint4(0u, 0u, 0u, 0u);
+            const int64_t grow = row0 + r;
+            if (grow < rows_valid)
+                v = *reinterpret_cast<const uint4 *>(X + grow * ldx + (int64_t)cc * 8);
+            const int j = cc / CPB, i = cc % CPB;
+            tile[r * cpr + j * CPB + chunk_slot<B>(i, j)] = v;
+            cc += dc;
+            r += dr;
+            if (cc >= cpr) { cc -= cpr; ++r; }
+        }
+    }
+    __syncthreads();
+
+    // 2. one Hadamard block per lane
+    const int r = t / nb, j = t - r * nb;
+    const bool active = r < rows;
+    float x[B];
+    float bmax = 0.0f;
+    if (active) {
+        if (perm == nullptr) {
+            const uint4 *src = tile + r * cpr + j * CPB;
+#pragma unroll
+            for (int i = 0; i < CPB; ++i) {
+                const uint4 v = src[chunk_slot<B>(i, j)];
+                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    stage1_packed(w[e], x[8 * i + 2 * e], x[8 * i + 2 * e + 1]);   // stage h = 1
+                }
             }
         } else {
-            for (int base = 0; base < cpr; base += a.stride) {
-                const int chunk = lane_c + base;
-                if (gather) {
-                    rotate_gathered(chunk, x[0]);
-                } else {
-                    uint4 v[4];
-                    load(chunk, v);
-                    rotate(v, x[0]);
-                }
-                store_codes<QB, WEIGHT>(x[0], rs, u, 4 * s, chunk, a.K, out, glive && chunk < cpr);
+            const uint16_t *rowh = reinterpret_cast<const uint16_t *>(tile + r * cpr);
+            const int32_t *p = perm + j * B;
+#pragma unroll
+            for (int e = 0; e < B; e += 2) {
+                const int k0 = p[e], k1 = p[e + 1];
+                const int c0 = k0 >> 3, c1 = k1 >> 3;
+                const int s0 = (c0 / CPB) * CPB + chunk_slot<B>(c0 % CPB, c0 / CPB);
+                const int s1 = (c1 / CPB) * CPB + chunk_slot<B>(c1 % CPB, c1 / CPB);
+                stage1_pair(rowh[s0 * 8 + (k0 & 7)], rowh[s1 * 8 + (k1 & 7)], x[e], x[e + 1]);
             }
+        }
+#pragma unroll
+        for (int h = 2; h < B; h <<= 1) {
+#pragma unroll
+            for (int i = 0; i < B; ++i) {
+                if ((i & h) == 0) {
+                    const float u = x[i], v = x[i + h];
+                    x[i] = u + v;
+                    x[i + h] = u - v;
+                }
+            }
+        }
+        bmax = block_absmax<B>(x);
+        atomicMax(&rowmax[r], __float_as_uint(bmax));
+    }
+    __syncthreads();
+    if (!active) return;
+
+    // 3. per-row scale and codes
+    const float a = __uint_as_float(rowmax[r]);
+    // the clip ratio: a launch argument, or read from device memory (a
+    // search that picks it on the GPU)
+    const float al = alpha_dev != nullptr ? *alpha_dev : alpha;
+    const float ac = WEIGHT ? al * a : a;
+    const float rc = (ac == 0.0f) ? 0.0f : Grid<QB>::qmax / ac;
+    const int64_t grow = row0 + r;
+    if (j == 0 && grow < rows_valid) scale_out[grow] = (ac / Grid<QB>::qmax) * post_scale;
+    if constexpr (QB == 8) {
+        store_q8<B, WEIGHT>(x, rc, grow, j, K, out);
+        return;
+    }
+
+    if constexpr (QB == 6) {
+        // fp6 layout: the codes as exact floats, six dwords per 32 codes
+        const int rho = WEIGHT ? wq_rho((int)(grow & 31)) : (int)(grow & 31);
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            float v = __builtin_fmaf(x[i], rc, kMagic);
+            if constexpr (WEIGHT) v = __builtin_amdgcn_fmed3f(v, kMagic - 7.0f, kMagic + 7.0f);
+            x[i] = v - kMagic;
+        }
+#pragma unroll
+        for (int c = 0; c < B / 32; ++c) {
+            const int64_t c32 = (int64_t)j * (B / 32) + c;
+            uint32_t w6[6];
+            f6_from_codes(&x[32 * c], w6);
+            f6_store(out + f6_unit_offset(grow >> 5, c32, K), f6_lane(c32, rho), w6);
+        }
+        return;
+    }
+    uint32_t words[B / 8];
+#pragma unroll
+    for (int g = 0; g < B / 8; ++g) {
+        uint32_t w[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            float v = __builtin_fmaf(x[8 * g + e], rc, kMagic);
+            if constexpr (WEIGHT) v = __builtin_amdgcn_fmed3f(v, kMagic - 7.0f, kMagic + 7.0f);
+            w[e] = __float_as_uint(v);
+        }
+        words[g] = pack8(w);
+    }
+
+    if constexpr (!WEIGHT) {
+        // packed activation layout: one 16-byte chunk per 32 codes
+#pragma unroll
+        for (int c = 0; c < B / 32; ++c) {
+            const int64_t c32 = (int64_t)j * (B / 32) + c;
+            *reinterpret_cast<uint4 *>(out + xq_chunk_offset(grow, c32, K)) =
+                make_uint4(words[4 * c], words[4 * c + 1], words[4 * c + 2], words[4 * c + 3]);
+        }
+    } else {
+        // packed weight layout: one 8-byte piece per k-group of 16 codes
+#pragma unroll
+        for (int g = 0; g < B / 16; ++g) {
+            const int64_t kg = (int64_t)j * (B / 16) + g;
+            uint2 *dst = reinterpret_cast<uint2 *>(out + wq_piece_offset(grow, kg, K));
+            *dst = make_uint2(words[2 * g], words[2 * g + 1]);
         }
     }
 }
 
 constexpr int kLdsLimit = 160 * 1024 - 1024;   // gathered rows of a workgroup (dynamic LDS)
 
-// Four-row groups per workgroup for rows of up to 8192 columns: the best lane
-// utilisation of whole waves (more groups on a tie, up to 8 and 1024 lanes),
-// but no more than leaves two workgroups per compute unit to the launch.
+// Four-row groups per workgroup for rows of up to 8192 columns: the most live
+// lanes on a compute unit, that is the lane utilisation of whole waves times
+// the share of the 28 waves a unit holds that whole workgroups of this size
+// fill: at 2048 columns 16-wave workgroups left 12 of them empty (20000 rows in
+// fp6 codes 30.7 us with them, 23.3 with 4-wave ones and the registers within
+// 28 waves).  More groups on a tie, up to 8 and 1024 lanes, but no more than
+// leaves two workgroups per compute unit to the launch.
 int pick_groups(int stride, int64_t total_groups, int cus) {
     int best = 1;
     double best_u = 0.0;
     for (int g = 1; g <= kMaxGroups && g * stride <= kMaxLanes; g <<= 1) {
         if (g > 1 && g * stride > 64 && total_groups / g < 2 * cus) break;
-        const double u = (double)(g * stride) / ((g * stride + 63) / 64 * 64);
+        const int waves = (g * stride + 63) / 64;
+        const double u = (double)(g * stride) * (28 / waves);
         if (u >= best_u) {
             best_u = u;
             best = g;
@@ -393,10 +567,10 @@ hipError_t launch_rq(RqArgs a, hipStream_t stream) {
         T = (a.groups * cpr + 63) / 64 * 64;
     } else {
         a.groups = 1;
-        a.stride = NCH == 2 ? ((cpr + 1) / 2 + 63) / 64 * 64 : kMaxLanes;
+        a.stride = ((cpr + 1) / 2 + 63) / 64 * 64;
         T = a.stride;
     }
-    const size_t lds = a.perm != nullptr && NCH != 0 ? (size_t)a.groups * a.K * 8 : 0;
+    const size_t lds = a.perm != nullptr ? (size_t)a.groups * a.K * 8 : 0;
     if (T > kMaxLanes || lds > kLdsLimit) return hipErrorInvalidConfiguration;
     if (lds > 65536 - 1024) {
         hipError_t e = hipFuncSetAttribute((const void *)rotate_quant_kernel<B, QB, WEIGHT, NCH>,
@@ -415,10 +589,24 @@ hipError_t launch_rq(RqArgs a, hipStream_t stream) {
 }
 
 template <int B, int QB, bool WEIGHT>
+hipError_t launch_rq_wide(const RqArgs &a, hipStream_t stream) {
+    const int T = (a.K / B + 63) / 64 * 64;
+    const size_t lds = (size_t)a.K * 2 + 4;
+    if (T > wide_max_threads<B>() || lds > 65536 + 4096) return hipErrorInvalidConfiguration;
+    hipError_t e = hipFuncSetAttribute((const void *)rotate_quant_wide_kernel<B, WEIGHT, QB>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, 65536 + 4096);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((rotate_quant_wide_kernel<B, WEIGHT, QB>), dim3((unsigned)a.rows_alloc, (unsigned)a.batch),
+                       dim3(T), lds, stream, a.X, a.ldx, a.perm, a.rows_valid, a.rows_alloc, a.K, 1, a.alpha,
+                       a.alpha_dev, a.post_scale, a.out, a.scale, a.out_stride, a.scale_stride);
+    return hipGetLastError();
+}
+
+template <int B, int QB, bool WEIGHT>
 hipError_t launch_rq_width(const RqArgs &a, hipStream_t stream) {
     if (a.K <= 8 * kMaxLanes) return launch_rq<B, QB, WEIGHT, 1>(a, stream);
     if (a.K <= 16 * kMaxLanes) return launch_rq<B, QB, WEIGHT, 2>(a, stream);
-    return launch_rq<B, QB, WEIGHT, 0>(a, stream);
+    return launch_rq_wide<B, QB, WEIGHT>(a, stream);
 }
 
 template <int B>
@@ -485,7 +673,7 @@ hipError_t launch_rotate_quant(const uint16_t *X, int64_t ldx, const int32_t *pe
                                float alpha, bool weight_mode, float post_scale,
                                uint8_t *out, float *scale, hipStream_t stream, int bits,
                                const float *alpha_dev, int batch, int64_t out_stride, int64_t scale_stride) {
-    if (batch > 1 && (!weight_mode || alpha_dev == nullptr)) return hipErrorInvalidValue;
+    if (batch > 1 && (!weight_mode || alpha_dev == nullptr || bits != 4)) return hipErrorInvalidValue;
     RqArgs a{};
     a.X = X;
     a.ldx = ldx;
