@@ -89,13 +89,14 @@ def gemm_ops(l):
 
 
 def rq_kernel_name(l, abits=4, codes="int4"):
-    """The activation kernel the library runs for this layer: the 8-row
-    kernel for rows of 2048..5120 codes at block 64, else the batched one
-    (code-width template argument 6: the 4-bit codes written as fp6)."""
+    """The activation kernel the library runs for this layer: one or two
+    8-column chunks per lane by the row length, one workgroup per row beyond
+    16384 columns (code-width template argument 6: the 4-bit codes written as
+    fp6)."""
     qb = 6 if (abits == 4 and codes == "fp6") else abits
-    if l.block == 64 and 2048 <= l.K <= 5120:
-        return f"rq_rows8_kernel<64, {qb}, false>"
-    return f"rq_act_kernel<{l.block}, {qb}, false>"
+    if l.K > 16384:
+        return f"rotate_quant_wide_kernel<{l.block}, false, {qb}>"
+    return f"rotate_quant_kernel<{l.block}, {qb}, false, {1 if l.K <= 8192 else 2}>"
 
 
 def load_traffic(path, kernel_src_sha):
@@ -115,12 +116,12 @@ def load_traffic(path, kernel_src_sha):
 
 
 def kernel_sha(codes="int4"):
-    """Hash of the GEMM kernel's source (the kernel the traffic figures
+    """Hash of the GEMM kernels' sources (the kernels the traffic figures
     describe)."""
     import hashlib
     h = hashlib.sha256()
-    src = "w4a4_gemm.hip" if codes == "int4" else "w4a4_f6.hip"
-    h.update(open(os.path.join(ROOT, "paper_2509_24416_amd", "csrc", src), "rb").read())
+    for src in ("tile_gemm.h", "w4a4_gemm.hip" if codes == "int4" else "w4a4_f6.hip"):
+        h.update(open(os.path.join(ROOT, "paper_2509_24416_amd", "csrc", src), "rb").read())
     return h.hexdigest()[:16]
 
 
@@ -758,12 +759,13 @@ def bench_stack(args, clq, torch, dev):
 # 4608 PixArt widths at token counts the block workloads do not use.
 SWEEP_KN = [(2048, 2048), (5120, 5120), (2560, 10240), (10240, 2560), (1152, 4608), (4608, 1152)]
 SWEEP_M = [512, 1536, 3072, 6144, 12288, 24576]
-SCHEDULES = {1: "persistent", 2: "persistent_whole_tiles", 3: "halves128", 4: "halves64"}
+SCHEDULES = {1: "split_k", 2: "whole_tiles", 3: "halves128", 4: "halves64"}
 
 
 def bench_gemm_schedule(args, clq, torch, dev):
     """The GEMM's automatic kernel choice against every forced schedule (the
-    CLQ_DEBUG_GEMM_SCHEDULE knob: persistent with and without split-k, the
+    CLQ_DEBUG_GEMM_SCHEDULE knob: k split over workgroups where that balances
+    the launch, whole tiles, the
     two-halves kernel on 128- and 64-token tiles) on shapes outside the block
     workloads.  HIP events around `reps` back-to-back launches per schedule,
     after warmup; every schedule computes the same result.  value = geometric
@@ -813,7 +815,7 @@ def bench_gemm_schedule(args, clq, torch, dev):
             best = min(forced, key=forced.get)
             ratio = forced[best] / times["auto"]
             ratios.append(ratio)
-            records.append({"M": M, "N": N, "K": K, "auto_kernel": ["persistent", "halves128", "halves64"][auto_plan["kernel"]],
+            records.append({"M": M, "N": N, "K": K, "auto_kernel": "split_k" if auto_plan["split_stages"] > 0 else "whole_tiles",
                             "auto_split": auto_plan["split_stages"] > 0, "us": times, "fastest_forced": best,
                             "fastest_over_auto": round(ratio, 4),
                             "auto_TOPS": round(2.0 * M * N * K / (times["auto"] * 1e-6) / 1e12, 1)})
@@ -927,15 +929,13 @@ def main():
     traffic = (load_traffic(TRAFFIC_FILES.get((wl.name, codes)), kernel_sha(codes))
                if (wbits, abits) == (4, 4) else None)
     plans = [clq.clq_w4a4_schedule(l.M, l.N, l.K) for l in layers] if (abits == 4 and codes == "int4") else None
+    # whole tiles (tile_gemm_kernel, or split_gemm_kernel where there are few);
+    # the int4 storage's k split over workgroups is w4a4_gemm_kernel
+    kinds = {"tile_gemm_kernel" if p is None or p["split_stages"] == 0 else "w4a4_gemm_kernel"
+             for p in plans or [None]}
+    gemm_name = " / ".join(sorted(kinds)) + " (mean over the 4 linears)"
     if codes == "fp6":
         plans = [{"kernel": clq.clq_w4a4_schedule_f6(l.M, l.N, l.K)} for l in layers]
-        kinds = sorted({clq.F6_SCHEDULES[p["kernel"]].split(" (")[0] for p in plans})
-        gemm_name = " / ".join(kinds) + " (mean over the 4 linears)"
-    elif abits == 4:
-        kinds = sorted({("w4a4_gemm_kernel" if p["kernel"] == 0 else "w4a4_gemm_halves_kernel") for p in plans})
-        gemm_name = " / ".join(kinds) + " (mean over the 4 linears)"
-    else:
-        gemm_name = f"a8_gemm_kernel<{wbits}> (mean over the 4 linears)"
     # the roofline prices a launch against the peak of the matrix
     # instruction it issues: int8 for the int4 path (codes widened to int8),
     # fp6 for the fp6-stored codes

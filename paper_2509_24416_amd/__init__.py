@@ -198,13 +198,13 @@ def clq_diag_mfma_probe_f6(ops, iters, grid, sink, stream=None):
     return grid * iters * 64 * 2 * 32 * 32 * 64
 
 
-F6_SCHEDULES = {1: "f6_gemm_kernel", 2: "f6_gemm_halves_kernel (128-token tiles)",
+F6_SCHEDULES = {1: "tile_gemm_kernel", 2: "f6_gemm_halves_kernel (128-token tiles)",
                 3: "f6_gemm_halves_kernel (64-token tiles)"}
 
 
 def clq_w4a4_schedule_f6(M, N, K):
-    """The fp6 GEMM kernel choice for an M x N x K product: 1 persistent
-    (256-token tiles), 2 / 3 two halves of the k loop (128- / 64-token tiles)."""
+    """The partition an M x N x K product falls into on the fp6 GEMM: 1 tiles
+    of 256 tokens, 2 / 3 two halves of the k loop on tiles of 128 / 64."""
     c = ctypes.c_int32()
     _check(_lib.clq_w4a4_schedule_f6(M, N, K, ctypes.byref(c)), "clq_w4a4_schedule_f6")
     return c.value
@@ -212,7 +212,7 @@ def clq_w4a4_schedule_f6(M, N, K):
 
 def clq_w4a4_schedule(M, N, K, with_workspace=True):
     """The GEMM schedule for an M x N x K product on the current device:
-    dict(kernel=0 persistent / 1 halves-128 / 2 halves-64, tiles, whole,
+    dict(kernel=0 / 1 / 2 for tiles of 256 / 128 / 64 tokens, tiles, whole,
     split_stages, grid)."""
     info = (ctypes.c_int64 * 5)()
     _check(_lib.clq_w4a4_schedule(M, N, K, 1 if with_workspace else 0, ctypes.cast(info, ctypes.c_void_p)),

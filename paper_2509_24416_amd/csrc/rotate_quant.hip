@@ -38,11 +38,12 @@
 //
 // Measured inside the block workloads (us; before: rows staged through LDS,
 // one Hadamard block per lane, pipelined batches): activations 4608 x 12288,
-// b = 128: 66.9 -> 42.0; 4608 x 3072: 17.5 -> 13.5; 8192 x 4608, b = 64: 27.4 ->
-// 25.3; 8192 x 1152: 11.3 -> 9.9; 1024 x 1152 (all launch and latency): 5.4 -> 4.7;
-// 43200 x 4608: 132.9 -> 126.5 (3.9 TB/s while the previous product's output
-// drains); weights 12288 x 3072, b = 128: 42.7 -> 18.9 for the whole call
-// (5.0 TB/s), whose 8-byte pieces used to go out one by one.
+// b = 128: 66.9 -> 38.1; 4608 x 3072: 17.5 -> 11.9; 43200 x 1152, b = 64: 33.5 ->
+// 29.3 to 32.2; 43200 x 4608: 132.9 -> 119.0 (4.2 TB/s while the previous
+// product's output drains); weights 12288 x 3072, b = 128: 42.7 -> 18.9 for the
+// whole call (5.0 TB/s), whose 8-byte pieces used to go out one by one.  Timed
+// alone, cached: 8192 x 1152 9.8 -> 8.2, 1024 x 1152 (all launch and latency)
+// 5.1 -> 3.8, gathered 7.1 -> 4.0.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
