@@ -759,6 +759,7 @@ def bench_stack(args, clq, torch, dev):
 # 4608 PixArt widths at token counts the block workloads do not use.
 SWEEP_KN = [(2048, 2048), (5120, 5120), (2560, 10240), (10240, 2560), (1152, 4608), (4608, 1152)]
 SWEEP_M = [512, 1536, 3072, 6144, 12288, 24576]
+GEMM_KERNELS = ["tiles256", "tiles128", "split4", "split2"]
 SCHEDULES = {1: "split_k", 2: "whole_tiles", 3: "halves128", 4: "halves64"}
 
 
@@ -792,7 +793,7 @@ def bench_gemm_schedule(args, clq, torch, dev):
             for force in (0, 1, 2, 3, 4):
                 clq.clq_debug_set(3, force)
                 plan = clq.clq_w4a4_schedule(M, N, K)
-                if force >= 3 and plan["kernel"] == 0:
+                if force >= 3 and K < 256:
                     continue   # k loop too short for the two-halves kernel
                 if force == 0:
                     auto_plan = plan
@@ -815,7 +816,7 @@ def bench_gemm_schedule(args, clq, torch, dev):
             best = min(forced, key=forced.get)
             ratio = forced[best] / times["auto"]
             ratios.append(ratio)
-            records.append({"M": M, "N": N, "K": K, "auto_kernel": "split_k" if auto_plan["split_stages"] > 0 else "whole_tiles",
+            records.append({"M": M, "N": N, "K": K, "auto_kernel": "split_k" if auto_plan["split_stages"] > 0 else GEMM_KERNELS[auto_plan["kernel"]],
                             "auto_split": auto_plan["split_stages"] > 0, "us": times, "fastest_forced": best,
                             "fastest_over_auto": round(ratio, 4),
                             "auto_TOPS": round(2.0 * M * N * K / (times["auto"] * 1e-6) / 1e12, 1)})
@@ -929,13 +930,14 @@ def main():
     traffic = (load_traffic(TRAFFIC_FILES.get((wl.name, codes)), kernel_sha(codes))
                if (wbits, abits) == (4, 4) else None)
     plans = [clq.clq_w4a4_schedule(l.M, l.N, l.K) for l in layers] if (abits == 4 and codes == "int4") else None
-    # whole tiles (tile_gemm_kernel, or split_gemm_kernel where there are few);
-    # the int4 storage's k split over workgroups is w4a4_gemm_kernel
-    kinds = {"tile_gemm_kernel" if p is None or p["split_stages"] == 0 else "w4a4_gemm_kernel"
-             for p in plans or [None]}
-    gemm_name = " / ".join(sorted(kinds)) + " (mean over the 4 linears)"
     if codes == "fp6":
         plans = [{"kernel": clq.clq_w4a4_schedule_f6(l.M, l.N, l.K)} for l in layers]
+        kinds = {clq.F6_SCHEDULES[p["kernel"]].split(" (")[0] for p in plans}
+    else:   # (the 8-bit settings choose as the int4 storage does without a workspace)
+        kinds = {"w4a4_gemm_kernel" if p["split_stages"] > 0 else
+                 "split_gemm_kernel" if p["kernel"] >= 2 else "tile_gemm_kernel"
+                 for p in plans or [clq.clq_w4a4_schedule(l.M, l.N, l.K, with_workspace=False) for l in layers]}
+    gemm_name = " / ".join(sorted(kinds)) + " (mean over the 4 linears)"
     # the roofline prices a launch against the peak of the matrix
     # instruction it issues: int8 for the int4 path (codes widened to int8),
     # fp6 for the fp6-stored codes

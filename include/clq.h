@@ -135,13 +135,14 @@ clq_status clq_rotate_quant_act(const void *X, int64_t ldx, const int32_t *perm,
  * workspace = NULL (whole tiles only, no waiting) or check the status. */
 size_t clq_w4a4_workspace_bytes(void);
 
-/* Diagnostic (host only, nothing enqueued): how clq_w4a4_linear partitions an
- * M x N x K product on the current device, with or without a workspace, as
- * info[0..4] = {partition (0: tiles of 256 tokens, 1 / 2: of 128 / 64), output
- * tiles of that size, tiles computed whole, k-stages (of 64 codes) split
- * across the grid, workgroups resident at once}.  With no k-stages split, a
- * workgroup may hold two neighbouring tiles of the partition, or compute one
- * with its k loop spread over its waves; the results do not depend on it. */
+/* Diagnostic (host only, nothing enqueued): the kernel clq_w4a4_linear runs
+ * for an M x N x K product on the current device, with or without a workspace
+ * and with the CLQ_DEBUG_GEMM_SCHEDULE knob's setting, as info[0..4] =
+ * {kernel (0: tiles of 256 tokens x 128 channels, 1: of 128, 2 / 3: of 64 with
+ * the k loop over four / two waves; with the knob at 3 / 4, 1 / 2 are the
+ * two-halves kernel on 128 / 64), output tiles of that size, tiles computed
+ * whole, k-stages (of 64 codes) split across the grid, workgroups resident at
+ * once}. */
 clq_status clq_w4a4_schedule(int64_t M, int64_t N, int64_t K, int32_t with_workspace, int64_t *info);
 
 /* Enqueues a copy of the workspace's split-k status words to `status`
@@ -277,11 +278,11 @@ clq_status clq_w4a4_linear_f6(const void *Xq, const float *x_scale, const void *
                               int64_t N, int64_t K, void *Y, int64_t ldy,
                               hipStream_t stream);
 
-/* Diagnostic (host only, nothing enqueued): the partition of an M x N x K
- * product for clq_w4a4_linear_f6 on the current device: *choice = 1 tiles of
- * 256 tokens, 2 / 3 of 128 / 64 (the CLQ_DEBUG_F6_SCHEDULE knob included; a
- * workgroup may hold two tiles, or spread one's k loop over its waves).
- * K >= 128. */
+/* Diagnostic (host only, nothing enqueued): the kernel clq_w4a4_linear_f6 runs
+ * for an M x N x K product on the current device (K >= 128): *choice = 1 tiles
+ * of 256 tokens, 2 / 3 the two-halves kernel on tiles of 128 / 64, 4 / 5 tiles
+ * of 64 with the k loop over four / two waves, 6 tiles of 128; 1, 2 and 3 are
+ * the settings of the CLQ_DEBUG_F6_SCHEDULE knob. */
 clq_status clq_w4a4_schedule_f6(int64_t M, int64_t N, int64_t K, int32_t *choice);
 
 /* Diagnostic: the exact integer sums of the fp6 operands as int32 [M][N],

@@ -198,22 +198,23 @@ def clq_diag_mfma_probe_f6(ops, iters, grid, sink, stream=None):
     return grid * iters * 64 * 2 * 32 * 32 * 64
 
 
-F6_SCHEDULES = {1: "tile_gemm_kernel", 2: "f6_gemm_halves_kernel (128-token tiles)",
-                3: "f6_gemm_halves_kernel (64-token tiles)"}
+F6_SCHEDULES = {1: "tile_gemm_kernel (256-token tiles)", 2: "f6_gemm_halves_kernel (128-token tiles)",
+                3: "f6_gemm_halves_kernel (64-token tiles)", 4: "split_gemm_kernel (k loop over 4 waves)",
+                5: "split_gemm_kernel (k loop over 2 waves)", 6: "tile_gemm_kernel (128-token tiles)"}
 
 
 def clq_w4a4_schedule_f6(M, N, K):
-    """The partition an M x N x K product falls into on the fp6 GEMM: 1 tiles
-    of 256 tokens, 2 / 3 two halves of the k loop on tiles of 128 / 64."""
+    """The kernel an M x N x K product runs on the fp6 GEMM: a key of F6_SCHEDULES."""
     c = ctypes.c_int32()
     _check(_lib.clq_w4a4_schedule_f6(M, N, K, ctypes.byref(c)), "clq_w4a4_schedule_f6")
     return c.value
 
 
 def clq_w4a4_schedule(M, N, K, with_workspace=True):
-    """The GEMM schedule for an M x N x K product on the current device:
-    dict(kernel=0 / 1 / 2 for tiles of 256 / 128 / 64 tokens, tiles, whole,
-    split_stages, grid)."""
+    """The kernel the GEMM runs for an M x N x K product on the current device:
+    dict(kernel=0 / 1 for tiles of 256 / 128 tokens, 2 / 3 of 64 with the k loop
+    over four / two waves, tiles, whole, split_stages, grid); with the schedule
+    knob at 3 / 4, kernel 1 / 2 is the two-halves kernel on 128 / 64."""
     info = (ctypes.c_int64 * 5)()
     _check(_lib.clq_w4a4_schedule(M, N, K, 1 if with_workspace else 0, ctypes.cast(info, ctypes.c_void_p)),
            "clq_w4a4_schedule")

@@ -139,15 +139,19 @@ extern int gemm_spin_limit;
 extern int gemm_drop_signal;
 extern int gemm_force_schedule;   // 0 automatic, 1..4 a forced GEMM kernel choice (debug knob)
 extern int f6_schedule_force;     // 0 automatic, 1..3 a forced fp6 GEMM kernel choice (debug knob)
-int f6_schedule(int64_t M, int64_t N, int K);   // the fp6 GEMM kernel a shape gets: 1, 2 or 3
+// the fp6 GEMM kernel a shape gets: tiles of 1 256 tokens, 2 / 3 128 / 64 (two
+// halves of the k loop), 4 / 5 64 (k loop over four / two waves), 6 128
+int f6_schedule(int64_t M, int64_t N, int K);
 
-// The W4A4 GEMM's schedule for a shape.  kernel: 0 the persistent kernel
-// (256-token tiles), 1 / 2 the two-halves kernel with 128- / 64-token tiles;
-// tiles: output tiles; dp: tiles computed whole (the persistent kernel's
-// first rounds); sk: k-stages split over the grid; grid: workgroups.
+// The W4A4 GEMM's schedule for a shape, for the launch and for the query.
+// kernel: tiles of 0 256, 1 128, 2 / 3 64 tokens (k loop over four / two waves),
+// or, with halves set, 1 / 2 the two-halves kernel on 128 / 64; tiles: output
+// tiles of that size; dp: tiles computed whole; sk: k-stages split over the
+// grid (256-token tiles only); grid: workgroups resident at once.
 struct GemmPlan {
-    int kernel, tiles_m, tiles, dp, sk, grid;
-    bool may_split;   // persistent kernel: whether the launch may split along k
+    int kernel;
+    bool halves;
+    int64_t tiles_m, tiles, dp, sk, grid;
 };
 // force: the schedule knob's value (0 automatic); the overload without it
 // reads the knob
@@ -158,7 +162,7 @@ int gemm_schedule_knob();
 // Rotate+quantize folded into the GEMM (the two-halves kernel's fused
 // variant): fused = 0 when the shape or arguments take two launches instead.
 struct RqGemmPlan {
-    int fused, kernel, tiles, rq_rows, n_rq;
+    int fused, kernel, tiles_m, tiles, rq_rows, n_rq;
 };
 RqGemmPlan plan_rq_gemm(int64_t M, int64_t N, int K, int block, bool have_workspace);
 

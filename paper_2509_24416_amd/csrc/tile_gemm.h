@@ -823,7 +823,10 @@ hipError_t launch(Args a, bool i32out, bool ragged, hipStream_t stream) {
 // 288: 9.1 over two waves, 10.1 over four; 1536, t = 216: 7.3 both), two up to 2 c,
 // and to 3 c on k loops under 48 stages (1280 x 1152 -> 3456: 11.9, 256-token tiles
 // 12.3; but 1536 x 3072 -> 3072: 21.2 / 20.1).
-enum Variant { kTile256, kTile128, kSplit4, kSplit2 };
+enum Variant { kTile256, kTile128, kSplit4, kSplit2, kVariants };
+// token tile, waves of a workgroup
+constexpr int kVariantTokens[kVariants] = {256, 128, 64, 64};
+constexpr int kVariantWaves[kVariants] = {4, 2, 4, 2};
 template <Fmt F>
 inline Variant pick_variant(int64_t M, int64_t N, int64_t K, int cus) {
     const int64_t t = (M + 63) / 64 * ((N + 127) / 128), c = cus, nks = K >> 6;
@@ -855,17 +858,21 @@ template <Fmt F> constexpr int kRing256 = F == Fmt::W4A4 ? 5 : F == Fmt::F6 ? 4 
 template <Fmt F> constexpr int kRing128 = F == Fmt::W4A4 ? 4 : 3;
 
 template <Fmt F>
-hipError_t launch_tiles(const Args &a, bool i32out, hipStream_t stream) {
+hipError_t launch_variant(Variant v, const Args &a, bool i32out, hipStream_t stream) {
     const bool ragged = a.N % 16 != 0;
-    switch (pick_variant<F>(a.M, a.N, a.K, compute_units())) {
+    switch (v) {
+        case kTile256: return launch<Cfg<F, 4, kRing256<F>>>(a, i32out, ragged, stream);
         case kTile128: return launch<Cfg<F, 2, kRing128<F>>>(a, i32out, ragged, stream);
-        case kSplit4:
-            return launch_split<SplitCfg<F, 4>>(a, i32out, ragged, stream);
-        case kSplit2:
-            return launch_split<SplitCfg<F, 2>>(a, i32out, ragged, stream);
-        case kTile256: break;
+        case kSplit4: return launch_split<SplitCfg<F, 4>>(a, i32out, ragged, stream);
+        case kSplit2: return launch_split<SplitCfg<F, 2>>(a, i32out, ragged, stream);
+        case kVariants: break;
     }
-    return launch<Cfg<F, 4, kRing256<F>>>(a, i32out, ragged, stream);
+    return hipErrorInvalidValue;
+}
+
+template <Fmt F>
+hipError_t launch_tiles(const Args &a, bool i32out, hipStream_t stream) {
+    return launch_variant<F>(pick_variant<F>(a.M, a.N, a.K, compute_units()), a, i32out, stream);
 }
 
 constexpr int kGroupPanels = 4;   // token panels per tile group

@@ -464,17 +464,6 @@ __global__ void repack_f6_kernel(const uint8_t *__restrict__ in, uint8_t *__rest
     f6_store(out + unit * kF6Unit, l, w);
 }
 
-int f6_device_cus() {
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-            cus = 256;
-    }
-    return cus;
-}
-
 }  // namespace
 
 hipError_t launch_repack_f6(const uint8_t *in, int64_t units, uint8_t *out, hipStream_t stream) {
@@ -508,30 +497,30 @@ hipError_t launch_gemm_f6_halves(F6Args g, bool i32out, bool ragged, hipStream_t
 
 int f6_schedule_force = 0;
 
-// The partition an M x N x K product falls into: 1 tiles of 256 tokens, 2 of
-// 128, 3 of 64 (what the query reports and the knob forces).  Without the knob
-// pick_variant (tile_gemm.h) chooses the kernel.
+// The kernel an M x N x K product gets, for the launch and for the query (the
+// numbers of clq_w4a4_schedule_f6; 1, 2 and 3 are what the knob forces).
 int f6_schedule(int64_t M, int64_t N, int K) {
     const int force = __atomic_load_n(&f6_schedule_force, __ATOMIC_RELAXED);
     if (force >= 1 && force <= 3) return force;
-    const int cus = f6_device_cus();
-    const int64_t tn = (N + 127) / 128;
-    const int64_t t256 = (M + 255) / 256 * tn, t128 = (M + 127) / 128 * tn;
-    if (t256 > cus) return 1;
-    return K >= 2048 && 2 * t128 <= cus ? 3 : 2;
-}
-
-hipError_t launch_gemm_f6(const uint8_t *Xq, const float *xs, const uint8_t *Wq, const float *ws,
-                          const uint16_t *bias, int64_t M, int64_t N, int K, void *Y, int64_t ldy, bool i32out,
-                          hipStream_t stream) {
-    const int force = __atomic_load_n(&f6_schedule_force, __ATOMIC_RELAXED);
     // Long k loops (48 stages or more) with more than one and at most two 128 x
     // 64 wave tiles per compute unit stay on the two halves, whose four waves
     // share the operands through LDS (2048 x 4608 -> 1152: 18.8 us, 19.4 with the
     // k loop over two waves, 20.6 over four, 25.2 on 256-token tiles).
     const int64_t waves = (M + 63) / 64 * ((N + 127) / 128), cus = tg::compute_units();
-    const bool halves = force == 0 && (K >> 6) >= 48 && waves > cus && waves <= 2 * cus;
-    if (force <= 1 && !halves) {
+    if ((K >> 6) >= 48 && waves > cus && waves <= 2 * cus) return 2;
+    switch (tg::pick_variant<tg::Fmt::F6>(M, N, K, (int)cus)) {
+        case tg::kTile128: return 6;
+        case tg::kSplit4: return 4;
+        case tg::kSplit2: return 5;
+        default: return 1;
+    }
+}
+
+hipError_t launch_gemm_f6(const uint8_t *Xq, const float *xs, const uint8_t *Wq, const float *ws,
+                          const uint16_t *bias, int64_t M, int64_t N, int K, void *Y, int64_t ldy, bool i32out,
+                          hipStream_t stream) {
+    const int choice = f6_schedule(M, N, K);
+    if (choice != 2 && choice != 3) {
         tg::Args t{};
         t.Xq = Xq;
         t.xs = xs;
@@ -544,9 +533,8 @@ hipError_t launch_gemm_f6(const uint8_t *Xq, const float *xs, const uint8_t *Wq,
         t.N = (int)N;
         t.K = K;
         t.group_m = tg::kGroupPanels;
-        if (force == 1)
-            return tg::launch<tg::Cfg<tg::Fmt::F6, 4, tg::kRing256<tg::Fmt::F6>>>(t, i32out, N % 16 != 0, stream);
-        return tg::launch_tiles<tg::Fmt::F6>(t, i32out, stream);
+        const tg::Variant v = choice == 6 ? tg::kTile128 : choice == 4 ? tg::kSplit4 : choice == 5 ? tg::kSplit2 : tg::kTile256;
+        return tg::launch_variant<tg::Fmt::F6>(v, t, i32out, stream);
     }
     F6Args g{};
     g.Xq = Xq;
@@ -560,8 +548,8 @@ hipError_t launch_gemm_f6(const uint8_t *Xq, const float *xs, const uint8_t *Wq,
     g.N = (int)N;
     g.K = K;
     const bool ragged = N % 16 != 0 || (bias && reinterpret_cast<uintptr_t>(bias) % 4 != 0);
-    return force == 2 || halves ? launch_gemm_f6_halves<F6Half128>(g, i32out, ragged, stream)
-                         : launch_gemm_f6_halves<F6Half64>(g, i32out, ragged, stream);
+    return choice == 2 ? launch_gemm_f6_halves<F6Half128>(g, i32out, ragged, stream)
+                       : launch_gemm_f6_halves<F6Half64>(g, i32out, ragged, stream);
 }
 
 }  // namespace clq

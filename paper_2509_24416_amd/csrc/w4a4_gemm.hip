@@ -1147,30 +1147,24 @@ hipError_t launch_halves(const GemmArgs &g, bool i32out, bool bias, bool rag, hi
     return hipGetLastError();
 }
 
-// The persistent kernel's schedule: whole tiles for all but the last one or
-// two rounds; when that fills the chip badly (and a workspace is given) the
-// rest is spread over every workgroup in k-stage units (1 to 2 tiles each).
-void plan_persistent(int ntiles, int nks, bool may_split, int &dp, int &sk, int &grid) {
-    grid = full_grid();
-    dp = ntiles;
-    sk = 0;
-    if (may_split && ntiles % grid != 0) {
-        const int d = max(0, ntiles / grid - 1) * grid;
-        const int64_t whole = (int64_t)((ntiles + grid - 1) / grid) * nks;
-        const int64_t split = (int64_t)(d / grid) * nks + ((int64_t)(ntiles - d) * nks + grid - 1) / grid;
-        const bool share_ok = (int64_t)(ntiles - d) * nks >= (int64_t)kSplitMinShare * grid;
-        if (share_ok && whole - split > kSplitMinSaved && 6 * (whole - split) > whole) {
-            dp = d;
-            sk = (ntiles - d) * nks;
-        }
-    }
-    if (sk == 0) grid = max(8, (min(ntiles, grid) + 7) / 8 * 8);
+// The split schedule (p: its 256-token tiles): whole tiles for all but the last
+// one or two rounds of the grid, the rest spread over every workgroup in
+// k-stage units (1 to 2 tiles each).  False where that does not pay.
+bool plan_split(GemmPlan &p, int nks) {
+    const int64_t grid = full_grid();
+    if (p.tiles % grid == 0) return false;
+    const int64_t d = std::max<int64_t>(0, p.tiles / grid - 1) * grid, left = (p.tiles - d) * nks;
+    const int64_t whole = (p.tiles + grid - 1) / grid * nks;
+    const int64_t split = d / grid * nks + (left + grid - 1) / grid;
+    if (left < kSplitMinShare * grid || whole - split <= kSplitMinSaved || 6 * (whole - split) <= whole) return false;
+    p.dp = d;
+    p.sk = left;
+    p.grid = grid;
+    return true;
 }
 
 template <class C, bool I32OUT, bool RAGGED, bool BIAS>
-hipError_t launch_cfg(GemmArgs g, bool may_split, hipStream_t stream) {
-    int grid;
-    plan_persistent(g.tiles_m * g.tiles_n, g.K >> 6, may_split, g.dp, g.sk, grid);
+hipError_t launch_cfg(const GemmArgs &g, int64_t grid, hipStream_t stream) {
     hipLaunchKernelGGL((w4a4_gemm_kernel<C, I32OUT, RAGGED, BIAS>), dim3((unsigned)grid), dim3(C::NT), 0, stream, g);
     return hipGetLastError();
 }
@@ -1181,50 +1175,61 @@ int gemm_schedule_knob() { return __atomic_load_n(&gemm_force_schedule, __ATOMIC
 
 GemmPlan plan_gemm(int64_t M, int64_t N, int K, bool may_split) { return plan_gemm(M, N, K, may_split, gemm_schedule_knob()); }
 
-// force: 0 automatic, 1 persistent, 2 persistent whole tiles, 3 / 4 the
-// two-halves kernel on 128- / 64-token tiles (the debug knob)
+namespace {
+
+// The two-halves kernel's partition of a shape: kernel 1 / 2 for tiles of 128 /
+// 64 tokens, 0 for none.  It decides which shapes the fused entry point runs as
+// one launch, and which are never split along k; the plain linear runs it only
+// where the schedule knob (force 3 / 4) asks.  The line was drawn by timing it
+// against a persistent kernel on 256-token tiles: at most 1.25 of those per
+// compute unit (one round of two workgroups per unit, or a short second one),
+// or k loops of 2048 codes and more, except on layers more than four times
+// wider than deep at more than 8 tiles per unit.
+struct HalvesPlan {
+    int kernel;
+    int64_t tiles_m, tiles;
+};
+HalvesPlan plan_halves(int64_t M, int64_t N, int K, int force) {
+    HalvesPlan p{};
+    const int64_t tiles_n = (N + TCfg::BN - 1) / TCfg::BN;
+    const int64_t ntiles = (M + TCfg::BM - 1) / TCfg::BM * tiles_n;
+    const bool deep = K >= 2048 && (N < 4 * (int64_t)K || ntiles <= 8 * device_cus());
+    if ((K >> 6) < kHalvesMinStages || force == 1 || force == 2) return p;
+    if (force == 0 && 4 * ntiles > 5 * device_cus() && !deep) return p;
+    // 128-token tiles (two four-wave workgroups per compute unit), or 64
+    // while those would fill at most half the compute units
+    const int64_t tm128 = (M + TileHalf128::BM - 1) / TileHalf128::BM;
+    p.kernel = force == 4 || (force != 3 && 2 * tm128 * tiles_n <= device_cus()) ? 2 : 1;
+    p.tiles_m = p.kernel == 2 ? (M + TileHalf64::BM - 1) / TileHalf64::BM : tm128;
+    p.tiles = p.tiles_m * tiles_n;
+    return p;
+}
+
+}  // namespace
+
+// force: 0 automatic, 1 tiles of 256 tokens with the split rule, 2 without it,
+// 3 / 4 the two-halves kernel on 128- / 64-token tiles (the debug knob)
 GemmPlan plan_gemm(int64_t M, int64_t N, int K, bool may_split, int force) {
     GemmPlan p{};
-    const int tiles_n = (int)((N + TCfg::BN - 1) / TCfg::BN);
-    const int ntiles = (int)((M + TCfg::BM - 1) / TCfg::BM) * tiles_n;
-    const bool halves_ok = (K >> 6) >= kHalvesMinStages;
-    // The partition (pick_variant in tile_gemm.h may run two of its tiles, or half
-    // of one, per workgroup; its halves kernel runs only where the knob or the
-    // fused entry point asks).  Smaller tiles:
-    // at most 1.25 256-token tiles per compute unit
-    // (just past one tile per CU the persistent kernel doubles up on a few
-    // CUs while the rest idle; the two-halves kernel fills one round of two
-    // workgroups per CU and runs a short second round on the remaining
-    // quarter at most), or long k loops (K >= 2048).  On such loops its
-    // 128-token tiles with the k range split between two halves of the
-    // workgroup beat the persistent kernel at every tile count measured,
-    // 2-16% (the schedule sweep over 36 shapes from 512 to 24576 tokens),
-    // except on layers more than four times wider than deep at more than 8
-    // tiles per compute unit, where the persistent kernel's grouped weight
-    // reuse wins.
-    const bool deep = K >= 2048 && (N < 4 * (int64_t)K || ntiles <= 8 * device_cus());
-    const bool halves = halves_ok && (force >= 3 || (force == 0 && (4 * ntiles <= 5 * device_cus() || deep)));
-    if (halves) {
-        // 128-token tiles (two four-wave workgroups per compute unit), or 64
-        // while those would fill at most half the compute units
-        const int tm128 = (int)((M + TileHalf128::BM - 1) / TileHalf128::BM);
-        if (force == 4 || (force != 3 && 2 * tm128 * tiles_n <= device_cus())) {
-            p.kernel = 2;
-            p.tiles_m = (int)((M + TileHalf64::BM - 1) / TileHalf64::BM);
-        } else {
-            p.kernel = 1;
-            p.tiles_m = tm128;
-        }
-        p.tiles = p.tiles_m * tiles_n;
-        p.dp = p.tiles;
-        p.grid = p.tiles;
+    const HalvesPlan h = plan_halves(M, N, K, force);
+    if (force >= 3 && h.kernel != 0) {
+        p.kernel = h.kernel;
+        p.halves = true;
+        p.tiles_m = h.tiles_m;
+        p.tiles = p.dp = h.tiles;
+        p.grid = std::min<int64_t>(p.tiles, 2 * device_cus());
         return p;
     }
-    p.kernel = 0;
-    p.tiles_m = (int)((M + TCfg::BM - 1) / TCfg::BM);
-    p.tiles = ntiles;
-    p.may_split = may_split && force != 2;
-    plan_persistent(ntiles, K >> 6, p.may_split, p.dp, p.sk, p.grid);
+    const int64_t tiles_n = (N + TCfg::BN - 1) / TCfg::BN;
+    p.tiles_m = (M + TCfg::BM - 1) / TCfg::BM;
+    p.tiles = p.tiles_m * tiles_n;
+    if (may_split && (force == 1 || (force == 0 && h.kernel == 0)) && plan_split(p, K >> 6)) return p;
+    const tg::Variant v = force == 0 ? tg::pick_variant<tg::Fmt::W4A4>(M, N, K, device_cus()) : tg::kTile256;
+    p.kernel = v;
+    p.tiles_m = (M + tg::kVariantTokens[v] - 1) / tg::kVariantTokens[v];
+    p.tiles = p.dp = p.tiles_m * tiles_n;
+    // (two waves on a SIMD: the kernels take more than half of its registers)
+    p.grid = std::min<int64_t>(p.tiles, (int64_t)device_cus() * 8 / tg::kVariantWaves[v]);
     return p;
 }
 
@@ -1339,7 +1344,6 @@ hipError_t launch_gemm(const uint8_t *Xq, const float *xs, const uint8_t *Wq, co
     g.M = (int)M;
     g.N = (int)N;
     g.K = K;
-    g.tiles_m = (int)((M + TCfg::BM - 1) / TCfg::BM);
     g.tiles_n = (int)((N + TCfg::BN - 1) / TCfg::BN);
     const size_t G = (size_t)full_grid();
     // workspace: status words | one flag per wave of every workgroup | one
@@ -1351,10 +1355,9 @@ hipError_t launch_gemm(const uint8_t *Xq, const float *xs, const uint8_t *Wq, co
     g.spin_limit = __atomic_load_n(&gemm_spin_limit, __ATOMIC_RELAXED);
     g.drop_signal = __atomic_load_n(&gemm_drop_signal, __ATOMIC_RELAXED);
     const GemmPlan pl = plan_gemm(M, N, K, workspace != nullptr, force);
-    const bool may_split = pl.may_split;
     // Whole tiles run on the shared tile kernels; what is left to the kernels of
     // this file: the split schedule, and the two halves where the knob asks.
-    if (pl.sk == 0 && force < 3) {
+    if (pl.sk == 0 && !pl.halves) {
         tg::Args t{};
         t.Xq = Xq;
         t.xs = xs;
@@ -1367,29 +1370,25 @@ hipError_t launch_gemm(const uint8_t *Xq, const float *xs, const uint8_t *Wq, co
         t.N = (int)N;
         t.K = K;
         t.group_m = tg::kGroupPanels;
-        if (force != 0)
-            return tg::launch<tg::Cfg<tg::Fmt::W4A4, 4, tg::kRing256<tg::Fmt::W4A4>>>(t, i32out, N % 16 != 0, stream);
-        return tg::launch_tiles<tg::Fmt::W4A4>(t, i32out, stream);
+        return tg::launch_variant<tg::Fmt::W4A4>((tg::Variant)pl.kernel, t, i32out, stream);
     }
-    if (pl.kernel == 2) {
-        g.tiles_m = pl.tiles_m;
-        return launch_halves<TileHalf64>(g, i32out, bias != nullptr, N % 16 != 0, stream);
-    }
-    if (pl.kernel == 1) {
-        g.tiles_m = pl.tiles_m;
-        return launch_halves<TileHalf128>(g, i32out, bias != nullptr, N % 16 != 0, stream);
-    }
+    g.tiles_m = (int)pl.tiles_m;
+    if (pl.halves)
+        return pl.kernel == 2 ? launch_halves<TileHalf64>(g, i32out, bias != nullptr, N % 16 != 0, stream)
+                              : launch_halves<TileHalf128>(g, i32out, bias != nullptr, N % 16 != 0, stream);
+    g.dp = (int)pl.dp;
+    g.sk = (int)pl.sk;
     // ragged channel edges, and biases not 4-byte aligned (the fast path
     // moves them in channel pairs), use element-wise epilogue accesses
     const bool ragged = N % 16 != 0 || (bias && reinterpret_cast<uintptr_t>(bias) % 4 != 0);
     if (i32out)
-        return ragged ? launch_cfg<TCfg, true, true, false>(g, may_split, stream)
-                      : launch_cfg<TCfg, true, false, false>(g, may_split, stream);
+        return ragged ? launch_cfg<TCfg, true, true, false>(g, pl.grid, stream)
+                      : launch_cfg<TCfg, true, false, false>(g, pl.grid, stream);
     if (ragged)
-        return bias ? launch_cfg<TCfg, false, true, true>(g, may_split, stream)
-                    : launch_cfg<TCfg, false, true, false>(g, may_split, stream);
-    return bias ? launch_cfg<TCfg, false, false, true>(g, may_split, stream)
-                : launch_cfg<TCfg, false, false, false>(g, may_split, stream);
+        return bias ? launch_cfg<TCfg, false, true, true>(g, pl.grid, stream)
+                    : launch_cfg<TCfg, false, true, false>(g, pl.grid, stream);
+    return bias ? launch_cfg<TCfg, false, false, true>(g, pl.grid, stream)
+                : launch_cfg<TCfg, false, false, false>(g, pl.grid, stream);
 }
 
 namespace {
@@ -1426,8 +1425,8 @@ constexpr int halves_pool_bytes() {
 
 RqGemmPlan plan_rq_gemm(int64_t M, int64_t N, int K, int block, bool have_workspace) {
     RqGemmPlan p{};
-    const GemmPlan g = plan_gemm(M, N, K, false);
-    if (!have_workspace || (g.kernel != 1 && g.kernel != 2) || N % 16 != 0) return p;
+    const HalvesPlan g = plan_halves(M, N, K, gemm_schedule_knob());
+    if (!have_workspace || g.kernel == 0 || N % 16 != 0) return p;
     const int T = g.kernel == 2 ? 2 * TileHalf64::NT : 2 * TileHalf128::NT;
     const int pool = g.kernel == 2 ? halves_pool_bytes<TileHalf64>() : halves_pool_bytes<TileHalf128>();
     const int nb = K / block;
@@ -1440,7 +1439,8 @@ RqGemmPlan plan_rq_gemm(int64_t M, int64_t N, int K, int block, bool have_worksp
     if (n_rq > kRqFlagInts) return p;
     p.fused = 1;
     p.kernel = g.kernel;
-    p.tiles = g.tiles;
+    p.tiles_m = (int)g.tiles_m;
+    p.tiles = (int)g.tiles;
     p.rq_rows = R;
     p.n_rq = (int)n_rq;
     return p;
@@ -1468,7 +1468,7 @@ hipError_t launch_rq_gemm(const uint16_t *X, int64_t ldx, int block, uint8_t *Xq
     g.N = (int)N;
     g.K = K;
     g.tiles_n = (int)((N + TCfg::BN - 1) / TCfg::BN);
-    g.tiles_m = p.tiles / g.tiles_n;
+    g.tiles_m = p.tiles_m;
     uint8_t *wsb = reinterpret_cast<uint8_t *>(workspace);
     g.status = reinterpret_cast<int *>(wsb);
     g.qhdr = reinterpret_cast<int *>(wsb) + 4;

@@ -226,21 +226,23 @@ def test_schedule(lib):
     assert lib.clq_w4a4_schedule(0, 8, 64, 1, ctypes.cast(info, ctypes.c_void_p)) == SHAPE
     assert lib.clq_w4a4_schedule(8, 8, 96, 1, ctypes.cast(info, ctypes.c_void_p)) == SHAPE
     assert lib.clq_w4a4_schedule(8, 8, 64, 1, None) == NULL
-    # 17 x 16 tiles of 256 tokens (<= 1.25 per CU): two halves, 128-token tiles
-    assert schedule(lib, 4352, 2048, 2432)[:2] == [1, 34 * 16]
-    # few tiles: 64-token tiles
-    assert schedule(lib, 1024, 1152, 1152)[:2] == [2, 16 * 9]
-    # long k loops (K >= 2048, N < 4 K): the two-halves kernel at any tile
-    # count -- the 28-block stack's fc2 at 16384 tokens, the video block's
-    # fc2 (43200 tokens), the FLUX-style block's linears
-    assert schedule(lib, 16384, 1152, 4608)[:2] == [1, 128 * 9]
-    assert schedule(lib, 43200, 1152, 4608)[:2] == [1, 338 * 9]
-    for N, K in ((9216, 3072), (3072, 3072), (3072, 12288)):
-        assert schedule(lib, 4608, N, K)[:2] == [1, 36 * (N // 128)]
-    # wide, shallow layers (N >= 4 K) too up to 8 tiles of 256 tokens per
-    # CU (the FLUX-style fc1: 6.75), the persistent kernel beyond
-    assert schedule(lib, 4608, 12288, 3072)[:2] == [1, 36 * 96]
-    assert schedule(lib, 6144, 10240, 2560)[:2] == [1, 48 * 80]
+    # in 128 x 64 wave tiles per compute unit: 4.25, tiles of 128 tokens
+    assert schedule(lib, 4352, 2048, 2432) == [1, 34 * 16, 34 * 16, 0, 34 * 16]
+    # 0.56: tiles of 64 tokens, the k loop over four waves
+    assert schedule(lib, 1024, 1152, 1152) == [2, 16 * 9, 16 * 9, 0, 16 * 9]
+    # 2.25: over two waves, or over four from 48 stages on
+    assert schedule(lib, 4096, 1152, 1152)[:2] == [3, 64 * 9]
+    assert schedule(lib, 4096, 1152, 4608)[:2] == [2, 64 * 9]
+    # 4.5 at 72 stages: over four waves; past 6 (the 28-block stack's fc2 at
+    # 16384 tokens, the video block's fc2 at 43200, the FLUX-style block's
+    # linears) tiles of 256 tokens, 512 workgroups resident
+    assert schedule(lib, 8192, 1152, 4608)[:2] == [2, 128 * 9]
+    assert schedule(lib, 16384, 1152, 4608) == [0, 64 * 9, 64 * 9, 0, 512]
+    assert schedule(lib, 43200, 1152, 4608) == [0, 169 * 9, 169 * 9, 0, 512]
+    for N, K in ((9216, 3072), (3072, 3072), (3072, 12288), (12288, 3072)):
+        assert schedule(lib, 4608, N, K)[:2] == [0, 18 * (N // 128)]
+    # long k loops never split, wide and shallow ones only past 8 tiles per CU
+    assert schedule(lib, 6144, 10240, 2560)[:2] == [0, 24 * 80]
     assert schedule(lib, 12288, 10240, 2560)[:2] == [0, 48 * 80]
     # 576 tiles of 30 stages: every k-stage split
     k, tiles, dp, sk, grid = schedule(lib, 16384, 1152, 1920)
@@ -251,7 +253,7 @@ def test_schedule(lib):
     # 1100 tiles: one whole round first, the last 588 tiles split
     assert schedule(lib, 11264, 3200, 1536) == [0, 1100, 512, 588 * 24, 512]
     # the PixArt block linears (M = 8192) and the video ones (M = 43200)
-    # take whole tiles on the persistent grid
+    # take whole tiles of 256 tokens
     for M, N, K in ((8192, 3456, 1152), (8192, 4608, 1152), (43200, 3456, 1152), (43200, 4608, 1152)):
         k, tiles, dp, sk, grid = schedule(lib, M, N, K)
         assert k == 0 and sk == 0 and dp == tiles
@@ -326,13 +328,17 @@ def f6_choice(lib, M, N, K):
 
 def test_f6_schedule_rule(lib):
     # 256 compute units (the MI355X's count, and the fallback without a GPU)
-    assert f6_choice(lib, 1024, 3456, 1152) == 2     # 108 tiles of 256 tokens: two halves, 128-token tiles
-    assert f6_choice(lib, 1024, 1152, 4608) == 3     # long k, 72 tiles of 128 tokens: 64-token tiles
-    assert f6_choice(lib, 4096, 1152, 4608) == 2     # 144 tiles of 256 tokens
-    assert f6_choice(lib, 4096, 3456, 1152) == 1     # 432 tiles: the persistent kernel
+    # in 128 x 64 wave tiles per compute unit
+    assert f6_choice(lib, 1024, 1152, 4608) == 4     # 0.56: k loop over four waves
+    assert f6_choice(lib, 1024, 3456, 1152) == 5     # 1.69: over two
+    assert f6_choice(lib, 2048, 1152, 4608) == 2     # 1.13, 72 stages: two halves of 128-token tiles
+    assert f6_choice(lib, 4096, 1152, 1152) == 5     # 2.25: over two
+    assert f6_choice(lib, 4096, 1152, 4608) == 1     # 2.25, 72 stages: 256-token tiles
+    assert f6_choice(lib, 8192, 1152, 4608) == 6     # 4.5: 128-token tiles
+    assert f6_choice(lib, 4096, 3456, 1152) == 1     # 6.75
     assert f6_choice(lib, 43200, 1152, 4608) == 1    # long k, many tiles
     assert f6_choice(lib, 43200, 3456, 1152) == 1
-    assert f6_choice(lib, 4608, 3072, 12288) == 1    # 432 tiles
+    assert f6_choice(lib, 4608, 3072, 12288) == 1
     c = ctypes.c_int32()
     assert lib.clq_w4a4_schedule_f6(4096, 1152, 4608, None) == NULL
     assert lib.clq_w4a4_schedule_f6(4096, 1152, 64, ctypes.byref(c)) == SHAPE
@@ -360,9 +366,9 @@ def test_schedule_knob(lib):
     assert lib.clq_debug_get(SCHED) == 0
     assert lib.clq_debug_set(SCHED, -1) == ARG and lib.clq_debug_set(SCHED, 5) == ARG
     try:
-        # 1: persistent with its split rule; 2: persistent, whole tiles only
+        # 1: 256-token tiles with the split rule; 2: whole tiles only
         assert lib.clq_debug_set(SCHED, 1) == OK and lib.clq_debug_get(SCHED) == 1
-        assert schedule(lib, 1024, 1152, 1152) == [0, 36, 36, 0, 40]
+        assert schedule(lib, 1024, 1152, 1152) == [0, 36, 36, 0, 36]
         assert schedule(lib, 16384, 1152, 4608) == [0, 576, 0, 576 * 72, 512]
         assert lib.clq_debug_set(SCHED, 2) == OK
         assert schedule(lib, 16384, 1152, 4608) == [0, 576, 576, 0, 512]
