@@ -1208,7 +1208,8 @@ HalvesPlan plan_halves(int64_t M, int64_t N, int K, int force) {
 }  // namespace
 
 // force: 0 automatic, 1 tiles of 256 tokens with the split rule, 2 without it,
-// 3 / 4 the two-halves kernel on 128- / 64-token tiles (the debug knob)
+// 3 / 4 the two-halves kernel on 128- / 64-token tiles (the debug knob; k loops
+// too short to halve keep the automatic choice)
 GemmPlan plan_gemm(int64_t M, int64_t N, int K, bool may_split, int force) {
     GemmPlan p{};
     const HalvesPlan h = plan_halves(M, N, K, force);
@@ -1220,6 +1221,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int K, bool may_split, int force) {
         p.grid = std::min<int64_t>(p.tiles, 2 * device_cus());
         return p;
     }
+    if (force >= 3) force = 0;
     const int64_t tiles_n = (N + TCfg::BN - 1) / TCfg::BN;
     p.tiles_m = (M + TCfg::BM - 1) / TCfg::BM;
     p.tiles = p.tiles_m * tiles_n;

@@ -379,7 +379,9 @@ def test_schedule_knob(lib):
         assert lib.clq_debug_set(SCHED, 4) == OK
         assert schedule(lib, 43200, 3456, 1152)[:2] == [2, 675 * 27]
         # k loops too short to halve (K < 256) keep the automatic choice
-        assert schedule(lib, 1024, 1152, 192)[0] == 0
+        forced = schedule(lib, 1024, 1152, 192)
+        assert lib.clq_debug_set(SCHED, 0) == OK and forced == schedule(lib, 1024, 1152, 192)
+        assert lib.clq_debug_set(SCHED, 4) == OK
         # the fused path follows the GEMM's schedule
         assert rq_schedule(lib, 1024, 1152, 1152, 64)[0] == 1
         assert lib.clq_debug_set(SCHED, 2) == OK
