@@ -326,9 +326,9 @@ hipError_t launch_clps(const uint16_t *X, int64_t ldx, const uint16_t *W, const 
     e = launch_rotate_quant(X, ldx, perm, M, padded_act_rows(M), K, block, 1.0f, false, 1.0f, xq, xs, stream);
     if (e != hipSuccess) return e;
     const int64_t wqs = (int64_t)l.wq_stride, wss = (int64_t)(l.ws_stride / 4);
-    // batches of nearly equal size, at most kQuantBatch candidates (and a
-    // tile count that fits an int)
-    const int most = (int)std::max<int64_t>(1, std::min<int64_t>(kQuantBatch, INT32_MAX / P));
+    // batches of nearly equal size, at most kQuantBatch candidates (and under
+    // 2^32 lanes of the error GEMM, 64 for each partial)
+    const int most = (int)std::max<int64_t>(1, std::min<int64_t>(kQuantBatch, UINT32_MAX / (64 * P)));
     const int batches = (grid + most - 1) / most;
     for (int i = 0, i0 = 0; i < batches; ++i) {
         const int nc = (grid - i0 + (batches - i) - 1) / (batches - i);

@@ -328,7 +328,7 @@ __device__ __forceinline__ void store_fragment(const Args &a, const Acc<F> &x, c
             hv[v / 2] = fma_mix2f((float)x[v] * xsc, ep[c0 + v], BIAS ? ep[BN + c0 + v] : 0.0f, (float)x[v + 1] * xsc,
                                   ep[c0 + v + 1], BIAS ? ep[BN + c0 + v + 1] : 0.0f);
         uint16_t *dst = reinterpret_cast<uint16_t *>(a.Y) + (int64_t)m * a.ldy + n0;
-        if (!RAGGED || n0 + 16 <= a.N) {
+        if (!RAGGED || n0 <= a.N - 16) {
             reinterpret_cast<v4u *>(dst)[0] = v4u{hv[0], hv[1], hv[2], hv[3]};
             reinterpret_cast<v4u *>(dst)[1] = v4u{hv[4], hv[5], hv[6], hv[7]};
         } else {
@@ -768,10 +768,13 @@ __global__ void __launch_bounds__(C::NT, 2) split_gemm_kernel(Args a)
     }
 }
 
+// (token and channel counts reach 2^31 - 1)
+inline int64_t tile_count(int64_t rows, int64_t tile) { return (rows + tile - 1) / tile; }
+
 template <class C>
 hipError_t launch_split(Args a, bool i32out, bool ragged, hipStream_t stream) {
-    a.tiles_m = (a.M + C::BM - 1) / C::BM;
-    a.tiles_n = (a.N + C::BN - 1) / C::BN;
+    a.tiles_m = (int)tile_count(a.M, C::BM);
+    a.tiles_n = (int)tile_count(a.N, C::BN);
     const dim3 grid((unsigned)(a.tiles_m * a.tiles_n)), block(C::NT);
     if (i32out && ragged) hipLaunchKernelGGL((split_gemm_kernel<C, true, true, false>), grid, block, 0, stream, a);
     else if (i32out) hipLaunchKernelGGL((split_gemm_kernel<C, true, false, false>), grid, block, 0, stream, a);
@@ -784,8 +787,8 @@ hipError_t launch_split(Args a, bool i32out, bool ragged, hipStream_t stream) {
 
 template <class C>
 hipError_t launch(Args a, bool i32out, bool ragged, hipStream_t stream) {
-    a.tiles_m = (a.M + C::BM - 1) / C::BM;
-    a.tiles_n = (a.N + C::BN - 1) / C::BN;
+    a.tiles_m = (int)tile_count(a.M, C::BM);
+    a.tiles_n = (int)tile_count(a.N, C::BN);
     const dim3 grid((unsigned)(a.tiles_m * a.tiles_n)), block(C::NT);
     if (i32out && ragged) hipLaunchKernelGGL((tile_gemm_kernel<C, true, true, false>), grid, block, 0, stream, a);
     else if (i32out) hipLaunchKernelGGL((tile_gemm_kernel<C, true, false, false>), grid, block, 0, stream, a);
@@ -817,7 +820,8 @@ hipError_t launch(Args a, bool i32out, bool ragged, hipStream_t stream) {
 //                           round of a few (3072 x 1152 -> 3456: 18.9 against 19.8;
 //                           4096 x 3072 -> 3072: 37.5 / 38.8);
 //   t > 6 c                 256-token tiles, which move the fewest operand bytes
-//                           (43200 x 1152 block: 590 us of GEMM against 690).
+//                           (43200 x 1152 block: 590 us of GEMM against 690), up
+//                           to 2^24 - 1 of them (a launch has under 2^32 lanes).
 // Splits need a stage for every wave.  fp6 operands are half again as large,
 // the matrix work half: four waves only pay up to t = c (2048 x 1152 -> 1152, t =
 // 288: 9.1 over two waves, 10.1 over four; 1536, t = 216: 7.3 both), two up to 2 c,
@@ -829,7 +833,8 @@ constexpr int kVariantTokens[kVariants] = {256, 128, 64, 64};
 constexpr int kVariantWaves[kVariants] = {4, 2, 4, 2};
 template <Fmt F>
 inline Variant pick_variant(int64_t M, int64_t N, int64_t K, int cus) {
-    const int64_t t = (M + 63) / 64 * ((N + 127) / 128), c = cus, nks = K >> 6;
+    const int64_t t = tile_count(M, 64) * tile_count(N, 128), c = cus, nks = K >> 6;
+    if (tile_count(M, 256) * tile_count(N, 128) >= (int64_t)1 << 24) return kTile128;
     if constexpr (F == Fmt::F6) {
         if (nks >= 4 && t <= c) return kSplit4;
         if (nks >= 2 && (t <= 2 * c || (t <= 3 * c && nks < 48))) return kSplit2;

@@ -1228,7 +1228,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int K, bool may_split, int force) {
     if (may_split && (force == 1 || (force == 0 && h.kernel == 0)) && plan_split(p, K >> 6)) return p;
     const tg::Variant v = force == 0 ? tg::pick_variant<tg::Fmt::W4A4>(M, N, K, device_cus()) : tg::kTile256;
     p.kernel = v;
-    p.tiles_m = (M + tg::kVariantTokens[v] - 1) / tg::kVariantTokens[v];
+    p.tiles_m = tg::tile_count(M, tg::kVariantTokens[v]);
     p.tiles = p.dp = p.tiles_m * tiles_n;
     // (two waves on a SIMD: the kernels take more than half of its registers)
     p.grid = std::min<int64_t>(p.tiles, (int64_t)device_cus() * 8 / tg::kVariantWaves[v]);

@@ -244,6 +244,11 @@ def test_schedule(lib):
     # long k loops never split, wide and shallow ones only past 8 tiles per CU
     assert schedule(lib, 6144, 10240, 2560)[:2] == [0, 24 * 80]
     assert schedule(lib, 12288, 10240, 2560)[:2] == [0, 48 * 80]
+    # the largest counts: tiles counted in 64 bits, launches of under 2^32 lanes
+    big = (1 << 31) - 1
+    assert schedule(lib, big, 8, 64)[:3] == [0, 1 << 23, 1 << 23]
+    assert schedule(lib, 8, big - 128, 64)[:2] == [0, (1 << 24) - 1]
+    assert schedule(lib, 8, big, 64)[:2] == [1, 1 << 24]
     # 576 tiles of 30 stages: every k-stage split
     k, tiles, dp, sk, grid = schedule(lib, 16384, 1152, 1920)
     assert (k, tiles, dp, sk, grid) == (0, 576, 0, 576 * 30, 512)
