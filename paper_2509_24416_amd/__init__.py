@@ -151,9 +151,11 @@ def _check(status, where):
 
 
 # The raw handle of a device's current stream.  Building the Stream object of
-# torch.cuda.current_stream() instead costs 2.7 us a call, a fifth of a small
-# linear's host time (a 256-token linear, quantizer and GEMM: 26 us -> 16).
-_raw_stream = torch._C._cuda_getCurrentRawStream
+# torch.cuda.current_stream() instead costs 2.7 us a call (with the buffer
+# checks done once, a 256-token linear, quantizer and GEMM: 26.3 us -> 17.5); a
+# torch without the private call takes that way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream",
+                      lambda device: torch.cuda.current_stream(device).cuda_stream)
 
 
 def _stream(stream):
