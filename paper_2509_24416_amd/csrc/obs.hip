@@ -416,6 +416,7 @@ hipError_t launch_obs_permutation(const float *scores, int D, int32_t *perm, hip
     const dim3 grid(1), block(kPermThreads);
     if (D <= 2 * kPermThreads) hipLaunchKernelGGL(obs_permutation_kernel<2>, grid, block, 0, stream, scores, D, perm);
     else if (D <= 8 * kPermThreads) hipLaunchKernelGGL(obs_permutation_kernel<8>, grid, block, 0, stream, scores, D, perm);
+    else if (D <= 16 * kPermThreads) hipLaunchKernelGGL(obs_permutation_kernel<16>, grid, block, 0, stream, scores, D, perm);
     else if (D <= 64 * kPermThreads) hipLaunchKernelGGL(obs_permutation_kernel<64>, grid, block, 0, stream, scores, D, perm);
     else return hipErrorInvalidValue;
     return hipGetLastError();

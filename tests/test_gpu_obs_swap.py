@@ -1,4 +1,4 @@
-"""GPU parity of the OBS swap at the edges of its kernel: one, two, eight and 64
+"""GPU parity of the OBS swap at the edges of its kernel: one, two, eight, 16 and 64
 channels per thread, ragged last threads, all scores equal, signed zeros,
 infinities and the type's largest and smallest values.  The swap is integer
 arithmetic on an order, so it matches the CPU oracle exactly; NaN scores, which
@@ -28,7 +28,7 @@ def swap(clq, sc):
     return out.cpu().numpy()
 
 
-@pytest.mark.parametrize("D", [2, 6, 1022, 1152, 2046, 2048, 2050, 8192, 8194, 32770, 65534])
+@pytest.mark.parametrize("D", [2, 6, 1022, 1152, 2046, 2048, 2050, 8192, 8194, 16384, 16386, 32770, 65534])
 def test_swap_values(clq, D):
     print(f"\n[gpu case] D = {D}", flush=True)
     rng = np.random.default_rng(D)
