@@ -529,13 +529,16 @@ constexpr int kLdsLimit = 160 * 1024 - 1024;   // gathered rows of a workgroup (
 // fill: at 2048 columns 16-wave workgroups left 12 of them empty (20000 rows in
 // fp6 codes 30.7 us with them, 23.3 with 4-wave ones and the registers within
 // 28 waves).  More groups on a tie, up to 8 and 1024 lanes, but no more than
-// leaves two workgroups per compute unit to the launch.
+// leaves two workgroups per compute unit to the launch, nor than 12 waves: of
+// 13 or 14, four on a SIMD, the unit's 7 a SIMD hold one workgroup and not two
+// (12000 rows of 3584 columns, b = 64: 25.2 us with 14 waves, 19.1 with 7).
 int pick_groups(int stride, int64_t total_groups, int cus) {
     int best = 1;
     double best_u = 0.0;
     for (int g = 1; g <= kMaxGroups && g * stride <= kMaxLanes; g <<= 1) {
         if (g > 1 && g * stride > 64 && total_groups / g < 2 * cus) break;
         const int waves = (g * stride + 63) / 64;
+        if (g > 1 && waves > 12) break;
         const double u = (double)(g * stride) * (28 / waves);
         if (u >= best_u) {
             best_u = u;
