@@ -315,8 +315,8 @@ rotate_quant_kernel(RqArgs a)
     }
 }
 
-// ---- rows of more than 16384 columns ---------------------------------------------
-// Four such rows do not fit a workgroup's registers.  One workgroup per row: the
+// ---- rows of more than 16384 columns, and few long rows ----------------------------
+// Four rows past 16384 columns do not fit a workgroup's registers.  One workgroup per row: the
 // row staged in LDS with coalesced 16-byte loads (each chunk of a Hadamard
 // block in an XOR-swizzled slot, so that the block reads hit distinct banks),
 // then one block per lane in registers.  Rotating twice with the kernel above
@@ -606,8 +606,30 @@ hipError_t launch_rq_wide(const RqArgs &a, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// Few long rows: up to this many take one workgroup each as well.  A lane of the
+// kernel above works through 32 or 64 values of four rows, whose latency is all
+// there is to a launch that leaves compute units idle; one Hadamard block a lane
+// is shorter while every row has a compute unit of its own, the more so the
+// smaller the block and the dearer the codes.  Measured on either side (us, one
+// workgroup a row / four rows): 64 x 16384, b = 32: 4.6 / 6.2, fp6 codes 4.9 / 7.4;
+// 256 rows 6.0 / 6.3, fp6 6.3 / 6.9, int8 7.5 / 6.4; 64 x 9216, b = 64: 4.6 / 5.5,
+// 384 rows 6.7 / 5.8; 64 x 9216, b = 128: 6.2 / 5.9; 64 x 4608, b = 32: 3.5 / 3.7, 384
+// rows 4.4 / 3.9, gathered 1.03 times the four rows' time, at 8192 columns 0.88.
+template <int B, int QB>
+int few_rows(int K, bool gather) {
+    if (K > 8 * kMaxLanes) {   // two chunks a lane
+        if (B == 128) return QB == 6 && !gather && K > 12288 ? 64 : 0;
+        if (B == 64) return (QB == 8 ? 128 : 192) - 64 * gather;
+        return QB == 8 ? 128 : QB == 4 && gather ? 192 : 256;
+    }
+    if (B != 32 || K <= (gather && QB != 6 ? 6144 : 4096)) return 0;
+    return QB == 8 || gather ? 128 : 192;
+}
+
 template <int B, int QB, bool WEIGHT>
 hipError_t launch_rq_width(const RqArgs &a, hipStream_t stream) {
+    if (a.batch == 1 && a.rows_alloc <= few_rows<B, QB>(a.K, a.perm != nullptr))
+        return launch_rq_wide<B, QB, WEIGHT>(a, stream);
     if (a.K <= 8 * kMaxLanes) return launch_rq<B, QB, WEIGHT, 1>(a, stream);
     if (a.K <= 16 * kMaxLanes) return launch_rq<B, QB, WEIGHT, 2>(a, stream);
     return launch_rq_wide<B, QB, WEIGHT>(a, stream);
