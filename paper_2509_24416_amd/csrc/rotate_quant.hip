@@ -521,6 +521,128 @@ rotate_quant_wide_kernel(const uint16_t *__restrict__ X, int64_t ldx,
     }
 }
 
+// ---- fp6 codes of rows of 4160 to 5120 columns, b = 64 ------------------------------
+// Such a row's chunks are 9 or 10 waves, of which a compute unit holds two
+// workgroups, 18 or 20 of its 28 waves, and in fp6 codes every store of four rows
+// is a 64-byte piece and a 32-byte tail.  Here a workgroup takes batches of 8 rows,
+// whose pieces are whole 128-byte lines: staged in LDS, one Hadamard block a lane
+// with the rows fastest, the next batch's loads in registers under this one's
+// work, one workgroup per compute unit.  Two barriers per batch: after the block
+// reads (the buffer may be refilled, and the previous maxima have been read) and
+// after the block maxima (codes may be formed).  Codes of a batch are formed at
+// the top of the next iteration, from the registers that still hold its rotated
+// blocks.  12000 rows, us, four rows a lane / here: 4352 columns 30.9 / 28.0, 4608
+// 30.9 / 28.9, 4864 33.9 / 29.9, 5120 34.2 / 31.0; 16384 x 4608 39.6 / 36.1 (5.8 TB/s of
+// 2 bytes in and 0.75 out, cached); nibble codes lose by it (12000
+// x 4608: 27.7 / 29.6).
+constexpr int kRows8 = 8, kRows8Lanes = kRows8 * 80;
+
+__global__ void __launch_bounds__(kRows8Lanes)
+rotate_quant_rows8_f6_kernel(const uint16_t *__restrict__ X, int64_t ldx, int64_t rows_valid, int64_t rows_alloc,
+                             int64_t nbatch, int K, uint8_t *__restrict__ out, float *__restrict__ scale_out)
+{
+    constexpr int R = kRows8, B = 64, CPB = B / 8;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int cpr = K >> 3, nb = K / B, chunks = R * cpr;
+    uint4 *tile = reinterpret_cast<uint4 *>(smem);
+    unsigned *rowmax = reinterpret_cast<unsigned *>(tile + chunks);   // [2][R]
+    const int t = threadIdx.x, T = blockDim.x;
+    const int64_t G = gridDim.x;
+
+    // this lane's chunks: source offset, and LDS slot | row << 16 | valid << 19
+    // (slots < 8 * 640)
+    int lsrc[CPB], lmeta[CPB];
+#pragma unroll
+    for (int k = 0; k < CPB; ++k) {
+        const int c = t + k * T;
+        const int r = c / cpr, cc = c - r * cpr;
+        lsrc[k] = r * (int)ldx + cc * 8;
+        const int jj = cc / CPB, ii = cc - jj * CPB;
+        lmeta[k] = c < chunks ? (r * cpr + jj * CPB + (ii ^ r)) | (r << 16) | (1 << 19) : 0;
+    }
+    uint4 ld[CPB];
+    auto load = [&](int64_t batch) {
+        const int64_t row0 = batch * R;
+        const uint16_t *base = X + row0 * ldx;
+#pragma unroll
+        for (int k = 0; k < CPB; ++k) {
+            ld[k] = make_uint4(0u, 0u, 0u, 0u);
+            if ((lmeta[k] >> 19) && row0 + ((lmeta[k] >> 16) & 7) < rows_valid)
+                ld[k] = *reinterpret_cast<const uint4 *>(base + lsrc[k]);
+        }
+    };
+    auto stash = [&]() {
+#pragma unroll
+        for (int k = 0; k < CPB; ++k)
+            if (lmeta[k] >> 19) tile[lmeta[k] & 0xFFFF] = ld[k];
+    };
+
+    const int j = t >> 3, r = t & 7;   // rows fastest
+    const bool active = j < nb;
+    int64_t b = blockIdx.x;
+    if (b >= nbatch) return;
+    if (t < 2 * R) rowmax[t] = 0u;
+    load(b);
+    stash();
+    if (b + G < nbatch) load(b + G);
+    __syncthreads();
+
+    float x[B];
+#pragma unroll
+    for (int e = 0; e < B; ++e) x[e] = 0.0f;
+    int64_t prev = -1;   // batch whose rotated blocks x holds, codes pending
+    int i = 0;
+    auto codes = [&](int64_t pb, int pi) {
+        const float a = __uint_as_float(rowmax[(pi & 1) * R + r]);
+        const float rc = (a == 0.0f) ? 0.0f : Grid<6>::qmax / a;
+        const int64_t grow = pb * R + r;
+        if (!active || grow >= rows_alloc) return;
+        if (j == 0 && grow < rows_valid) scale_out[grow] = a / Grid<6>::qmax;
+#pragma unroll
+        for (int e = 0; e < B; ++e) x[e] = __builtin_fmaf(x[e], rc, kMagic) - kMagic;
+#pragma unroll
+        for (int c = 0; c < B / 32; ++c) {
+            const int64_t c32 = (int64_t)j * (B / 32) + c;
+            uint32_t w6[6];
+            f6_from_codes(&x[32 * c], w6);
+            f6_store(out + f6_unit_offset(grow >> 5, c32, K), f6_lane(c32, (int)(grow & 31)), w6);
+        }
+    };
+
+    for (; b < nbatch; ++i, b += G) {
+        if (prev >= 0) codes(prev, i - 1);
+        if (active) {
+            const uint4 *src = tile + r * cpr + j * CPB;
+#pragma unroll
+            for (int ii = 0; ii < CPB; ++ii) {
+                const uint4 v = src[ii ^ r];
+                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) stage1_packed(w[e], x[8 * ii + 2 * e], x[8 * ii + 2 * e + 1]);
+            }
+        }
+        __syncthreads();   // every block read and every read of the previous maxima done
+        if (t < R) rowmax[((i + 1) & 1) * R + t] = 0u;   // the next batch's, read last by the codes above
+        if (active) {
+#pragma unroll
+            for (int h = 2; h < B; h <<= 1)
+#pragma unroll
+                for (int ii = 0; ii < B; ++ii)
+                    if ((ii & h) == 0) {
+                        const float u = x[ii], v = x[ii + h];
+                        x[ii] = u + v;
+                        x[ii + h] = u - v;
+                    }
+            atomicMax(&rowmax[(i & 1) * R + r], __float_as_uint(block_absmax<B>(x)));
+        }
+        if (b + G < nbatch) stash();
+        if (b + 2 * G < nbatch) load(b + 2 * G);
+        __syncthreads();   // maxima complete, next batch staged
+        prev = b;
+    }
+    if (prev >= 0) codes(prev, i - 1);
+}
+
 constexpr int kLdsLimit = 160 * 1024 - 1024;   // gathered rows of a workgroup (dynamic LDS)
 
 // Four-row groups per workgroup for rows of up to 8192 columns: the most live
@@ -626,8 +748,34 @@ int few_rows(int K, bool gather) {
     return QB == 8 || gather ? 128 : 192;
 }
 
+// Two or more rounds of a batch per compute unit, five sixths full (4608 columns,
+// four rows a lane / batches: 2048 rows, one round, 7.4 / 7.7; 2560, 1.25 rounds, 9.1 /
+// 11.0; 3700, 1.8, 13.8 / 12.4; 5000, 2.4, 15.8 / 17.1; 6000, 2.9, 18.3 / 17.9).
+bool rows8_fills(int64_t batches, int64_t cus) {
+    const int64_t rounds = (batches + cus - 1) / cus;
+    return rounds >= 2 && 6 * batches >= 5 * rounds * cus;
+}
+
+hipError_t launch_rq_rows8_f6(const RqArgs &a, hipStream_t stream) {
+    const int T = (kRows8 * (a.K / 64) + 63) / 64 * 64;
+    const size_t lds = (size_t)kRows8 * a.K * 2 + 2 * kRows8 * 4;
+    if (T > kRows8Lanes || lds > kLdsLimit) return hipErrorInvalidConfiguration;
+    hipError_t e = hipFuncSetAttribute((const void *)rotate_quant_rows8_f6_kernel,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit);
+    if (e != hipSuccess) return e;
+    const int64_t nbatch = (a.rows_alloc + kRows8 - 1) / kRows8;
+    hipLaunchKernelGGL(rotate_quant_rows8_f6_kernel, dim3((unsigned)std::min<int64_t>(nbatch, rq_cus())), dim3(T), lds,
+                       stream, a.X, a.ldx, a.rows_valid, a.rows_alloc, nbatch, a.K, a.out, a.scale);
+    return hipGetLastError();
+}
+
 template <int B, int QB, bool WEIGHT>
 hipError_t launch_rq_width(const RqArgs &a, hipStream_t stream) {
+    // (32-bit offsets within a batch)
+    if constexpr (B == 64 && QB == 6 && !WEIGHT)
+        if (a.perm == nullptr && a.K > 4096 && a.K <= 64 * (kRows8Lanes / kRows8) && kRows8 * a.ldx <= INT32_MAX &&
+            rows8_fills(a.rows_alloc / kRows8, rq_cus()))
+            return launch_rq_rows8_f6(a, stream);
     if (a.batch == 1 && a.rows_alloc <= few_rows<B, QB>(a.K, a.perm != nullptr))
         return launch_rq_wide<B, QB, WEIGHT>(a, stream);
     if (a.K <= 8 * kMaxLanes) return launch_rq<B, QB, WEIGHT, 1>(a, stream);

@@ -3,8 +3,9 @@
 A lane owns 8 columns of four rows; the widths below change how many four-row
 groups share a workgroup (1, 2, 4, 8, groups that end inside a wave), how many
 chunks a lane holds (one up to 8192 columns, two up to 16384, none beyond), where
-a gathered row is staged, and which few rows take a workgroup each.  Codes and
-scales match the CPU oracle bit for bit, padding rows hold zero codes.
+a gathered row is staged, and which few rows take a workgroup each, or
+run in batches of 8.  Codes and scales match the CPU oracle bit for bit, padding
+rows hold zero codes.
 """
 import numpy as np
 import pytest
@@ -40,7 +41,10 @@ def host(t):
     (35, 8192, 128), (33, 8256, 64), (31, 8320, 128), (5, 16384, 32), (3, 16448, 64), (2, 32768, 128),
     # the last row counts with a workgroup each, and the first without
     (128, 4160, 32), (192, 4160, 32), (193, 4160, 32), (128, 6208, 32), (256, 8256, 32), (257, 8256, 32),
-    (128, 8256, 64), (192, 8256, 64), (193, 8256, 64), (64, 12416, 128), (65, 12416, 128)])
+    (128, 8256, 64), (192, 8256, 64), (193, 8256, 64), (64, 12416, 128), (65, 12416, 128),
+    # fp6 rows in batches of 8: the first row count of 256 compute units' second
+    # round that takes them and the last that does not, ragged last batches
+    (3393, 4160, 64), (3392, 4160, 64), (4070, 5120, 64), (6001, 4608, 64), (4096, 5184, 64)])
 def test_codes_and_scales(clq, M, K, block, with_perm):
     print(f"\n[gpu case] {M} x {K}, block {block}, perm {with_perm}", flush=True)
     X = workloads.activations(M, K, "L1", seed=M + K + block)
