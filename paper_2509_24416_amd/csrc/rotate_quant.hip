@@ -522,19 +522,20 @@ rotate_quant_wide_kernel(const uint16_t *__restrict__ X, int64_t ldx,
 }
 
 // ---- fp6 codes of rows of 4160 to 5120 columns, b = 64 ------------------------------
-// Such a row's chunks are 9 or 10 waves, of which a compute unit holds two
-// workgroups, 18 or 20 of its 28 waves, and in fp6 codes every store of four rows
-// is a 64-byte piece and a 32-byte tail.  Here a workgroup takes batches of 8 rows,
+// Such a row's chunks are 9 waves, the last of them partly empty, or 10, of which a
+// compute unit holds 20 of its 28, and in fp6 codes every store of four rows is a
+// 64-byte piece and a 32-byte tail.  Here a workgroup takes batches of 8 rows,
 // whose pieces are whole 128-byte lines: staged in LDS, one Hadamard block a lane
 // with the rows fastest, the next batch's loads in registers under this one's
 // work, one workgroup per compute unit.  Two barriers per batch: after the block
 // reads (the buffer may be refilled, and the previous maxima have been read) and
 // after the block maxima (codes may be formed).  Codes of a batch are formed at
 // the top of the next iteration, from the registers that still hold its rotated
-// blocks.  12000 rows, us, four rows a lane / here: 4352 columns 30.9 / 28.0, 4608
-// 30.9 / 28.9, 4864 33.9 / 29.9, 5120 34.2 / 31.0; 16384 x 4608 39.6 / 36.1 (5.8 TB/s of
-// 2 bytes in and 0.75 out, cached); nibble codes lose by it (12000
-// x 4608: 27.7 / 29.6).
+// blocks.  16384 rows, us, four rows a lane / here, inputs from memory: 4160 columns
+// 43.7 / 39.9, 4352 44.4 / 41.0, 4864 48.5 / 45.9 (4.8 TB/s), 5120 49.2 / 47.4; the 9
+// full waves of 4608 columns, 27 of them resident, gain 3% by themselves (44.6 / 43.3)
+// and nothing behind a GEMM (a block 341.0 / 343.3), and nibble codes lose (12000 x
+// 4608: 27.7 / 29.6).
 constexpr int kRows8 = 8, kRows8Lanes = kRows8 * 80;
 
 __global__ void __launch_bounds__(kRows8Lanes)
@@ -748,9 +749,9 @@ int few_rows(int K, bool gather) {
     return QB == 8 || gather ? 128 : 192;
 }
 
-// Two or more rounds of a batch per compute unit, five sixths full (4608 columns,
-// four rows a lane / batches: 2048 rows, one round, 7.4 / 7.7; 2560, 1.25 rounds, 9.1 /
-// 11.0; 3700, 1.8, 13.8 / 12.4; 5000, 2.4, 15.8 / 17.1; 6000, 2.9, 18.3 / 17.9).
+// Two or more rounds of a batch per compute unit, five sixths full (4864 columns,
+// cached, four rows a lane / batches: 2560 rows, 1.25 rounds, 10.1 / 11.2; 3700, 1.8,
+// 15.4 / 13.1; 5000, 2.4, 17.6 / 17.7; 6000, 2.9, 21.0 / 18.6).
 bool rows8_fills(int64_t batches, int64_t cus) {
     const int64_t rounds = (batches + cus - 1) / cus;
     return rounds >= 2 && 6 * batches >= 5 * rounds * cus;
@@ -773,8 +774,8 @@ template <int B, int QB, bool WEIGHT>
 hipError_t launch_rq_width(const RqArgs &a, hipStream_t stream) {
     // (32-bit offsets within a batch)
     if constexpr (B == 64 && QB == 6 && !WEIGHT)
-        if (a.perm == nullptr && a.K > 4096 && a.K <= 64 * (kRows8Lanes / kRows8) && kRows8 * a.ldx <= INT32_MAX &&
-            rows8_fills(a.rows_alloc / kRows8, rq_cus()))
+        if (a.perm == nullptr && a.K > 4096 && a.K <= 64 * (kRows8Lanes / kRows8) && a.K != 8 * 9 * 64 &&
+            kRows8 * a.ldx <= INT32_MAX && rows8_fills(a.rows_alloc / kRows8, rq_cus()))
             return launch_rq_rows8_f6(a, stream);
     if (a.batch == 1 && a.rows_alloc <= few_rows<B, QB>(a.K, a.perm != nullptr))
         return launch_rq_wide<B, QB, WEIGHT>(a, stream);

@@ -44,7 +44,7 @@ def host(t):
     (128, 8256, 64), (192, 8256, 64), (193, 8256, 64), (64, 12416, 128), (65, 12416, 128),
     # fp6 rows in batches of 8: the first row count of 256 compute units' second
     # round that takes them and the last that does not, ragged last batches
-    (3393, 4160, 64), (3392, 4160, 64), (4070, 5120, 64), (6001, 4608, 64), (4096, 5184, 64)])
+    (3393, 4160, 64), (3392, 4160, 64), (4070, 5120, 64), (6001, 4544, 64), (4096, 4608, 64), (4096, 5184, 64)])
 def test_codes_and_scales(clq, M, K, block, with_perm):
     print(f"\n[gpu case] {M} x {K}, block {block}, perm {with_perm}", flush=True)
     X = workloads.activations(M, K, "L1", seed=M + K + block)
