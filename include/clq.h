@@ -281,8 +281,9 @@ clq_status clq_w4a4_linear_f6(const void *Xq, const float *x_scale, const void *
 /* Diagnostic (host only, nothing enqueued): the kernel clq_w4a4_linear_f6 runs
  * for an M x N x K product on the current device (K >= 128): *choice = 1 tiles
  * of 256 tokens, 2 / 3 the two-halves kernel on tiles of 128 / 64, 4 / 5 tiles
- * of 64 with the k loop over four / two waves, 6 tiles of 128; 1, 2 and 3 are
- * the settings of the CLQ_DEBUG_F6_SCHEDULE knob. */
+ * of 64 with the k loop over four / two waves, 6 tiles of 128, 7 tiles of 256 on
+ * a persistent grid (1 where the bias is not 4-byte aligned); 1, 2 and 3 are the
+ * settings of the CLQ_DEBUG_F6_SCHEDULE knob. */
 clq_status clq_w4a4_schedule_f6(int64_t M, int64_t N, int64_t K, int32_t *choice);
 
 /* Diagnostic: the exact integer sums of the fp6 operands as int32 [M][N],

@@ -202,7 +202,8 @@ def clq_diag_mfma_probe_f6(ops, iters, grid, sink, stream=None):
 
 F6_SCHEDULES = {1: "tile_gemm_kernel (256-token tiles)", 2: "f6_gemm_halves_kernel (128-token tiles)",
                 3: "f6_gemm_halves_kernel (64-token tiles)", 4: "split_gemm_kernel (k loop over 4 waves)",
-                5: "split_gemm_kernel (k loop over 2 waves)", 6: "tile_gemm_kernel (128-token tiles)"}
+                5: "split_gemm_kernel (k loop over 2 waves)", 6: "tile_gemm_kernel (128-token tiles)",
+                7: "f6_gemm_kernel (256-token tiles, persistent grid)"}
 
 
 def clq_w4a4_schedule_f6(M, N, K):

@@ -140,7 +140,8 @@ extern int gemm_drop_signal;
 extern int gemm_force_schedule;   // 0 automatic, 1..4 a forced GEMM kernel choice (debug knob)
 extern int f6_schedule_force;     // 0 automatic, 1..3 a forced fp6 GEMM kernel choice (debug knob)
 // the fp6 GEMM kernel a shape gets: tiles of 1 256 tokens, 2 / 3 128 / 64 (two
-// halves of the k loop), 4 / 5 64 (k loop over four / two waves), 6 128
+// halves of the k loop), 4 / 5 64 (k loop over four / two waves), 6 128, 7 256 on
+// a persistent grid
 int f6_schedule(int64_t M, int64_t N, int K);
 
 // The W4A4 GEMM's schedule for a shape, for the launch and for the query.

@@ -342,7 +342,15 @@ def test_f6_schedule_rule(lib):
     assert f6_choice(lib, 8192, 1152, 4608) == 6     # 4.5: 128-token tiles
     assert f6_choice(lib, 4096, 3456, 1152) == 1     # 6.75
     assert f6_choice(lib, 43200, 1152, 4608) == 1    # long k, many tiles
-    assert f6_choice(lib, 43200, 3456, 1152) == 1
+    # past 6 and 12 stages at most, 18 on many token panels: a persistent grid
+    assert f6_choice(lib, 4096, 3456, 768) == 7 and f6_choice(lib, 4096, 3456, 832) == 1
+    assert f6_choice(lib, 43200, 3456, 1152) == 7 and f6_choice(lib, 43200, 3456, 1216) == 1
+    assert f6_choice(lib, 32768, 3456, 1152) == 1
+    assert f6_choice(lib, 4096, 3072, 768) == 6
+    assert f6_choice(lib, 20480, 1008, 512) == 7 and f6_choice(lib, 20480, 1040, 512) == 1   # channels in whole tiles
+    assert f6_choice(lib, 36000, 4608, 192) == 7 and f6_choice(lib, 37000, 4608, 192) == 1   # 316, 325 MiB of output
+    assert f6_choice(lib, 37000, 4608, 256) == 7
+    assert f6_choice(lib, 16384, 12288, 256) == 1 and f6_choice(lib, 16640, 12288, 256) == 7
     assert f6_choice(lib, 4608, 3072, 12288) == 1
     c = ctypes.c_int32()
     assert lib.clq_w4a4_schedule_f6(4096, 1152, 4608, None) == NULL

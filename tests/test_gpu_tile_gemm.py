@@ -5,7 +5,8 @@ units assumed): the k loop over four waves up to t = 512 (and to 1280 on k
 loops of 48 stages of 64 codes or more), over two up to 768, tiles of 256
 tokens up to 1024, of 128 up to 1536, of 256 beyond; fp6 codes take four waves
 to 256, two to 512 (768 under 48 stages), and two halves of a workgroup from 256
-to 512 on longer k loops; fewer stages than waves fall through to the next
+to 512 on longer k loops, and a persistent grid past 1536 on k loops of at most
+12 or 18 stages (one tile a workgroup, several, tiles that end mid-stream); fewer stages than waves fall through to the next
 choice.  Shapes sit on both sides of each line, with
 ragged token and channel counts and stage counts that leave remainders, for
 every code storage.  Sums are integers and exact.  An fp16 output is one
@@ -31,7 +32,9 @@ def clq():
 
 SHAPES = [(1, 16, 128), (33, 130, 128), (65, 200, 192), (300, 1000, 256), (257, 1009, 448), (2000, 2040, 320),
           (2100, 2048, 256), (1500, 4000, 192), (2120, 3072, 320), (4000, 2050, 128), (2040, 3968, 3072),
-          (1100, 3072, 256), (1100, 3000, 3072), (2100, 4090, 192), (2560, 3072, 3136), (6200, 2000, 256), (6208, 2050, 128)]
+          (1100, 3072, 256), (1100, 3000, 3072), (2100, 4090, 192), (2560, 3072, 3136), (6200, 2000, 256), (6208, 2050, 128),
+          (6201, 2048, 128), (4097, 3456, 192), (16384, 1152, 320), (12800, 2176, 768), (2049, 8320, 448),
+          (25700, 1024, 1152), (12801, 1008, 128), (12801, 1040, 128)]
 
 
 def _codes(clq, fmt, x, w, M, N, K, block):
@@ -84,4 +87,17 @@ def test_sums_and_outputs(clq, M, N, K, fmt):
         bound = 2.0 ** -11 * y.abs() + 2.0 ** -23 * p.abs() + 2.0 ** -25
         got = linear(b).double()
         assert bool(((got - y).abs() <= bound).all())
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("fmt", ["w4a4", "f6"])
+@pytest.mark.parametrize("M,N,K", [(300, 1008, 256), (6201, 2048, 128)])
+def test_bias_of_two_byte_alignment(clq, M, N, K, fmt):
+    print(f"\n[gpu case] {fmt} {M} x {K} -> {N}, bias at an odd element", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M)
+    x = torch.randn((M, K), generator=g, device="cuda").half()
+    w = torch.randn((N, K), generator=g, device="cuda").half()
+    bias = torch.randn(N + 1, generator=g, device="cuda").half()
+    linear = _codes(clq, fmt, x, w, M, N, K, 64)[-1]
+    assert torch.equal(linear(bias[1:]), linear(bias[1:].clone()))
     torch.cuda.synchronize()
