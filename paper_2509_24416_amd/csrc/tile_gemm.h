@@ -815,7 +815,10 @@ hipError_t launch(Args a, bool i32out, bool ragged, hipStream_t stream) {
 //                           4608 -> 1152: 40.9 / 46.0; 2048 x 3072 -> 3072, t = 768: 21.6,
 //                           22.2 over two), up to t = 5 c;
 //   3 c < t <= 4 c          256-token tiles, half a round (1536 x 1152 -> 4608: 13.4,
-//                           k over two waves 13.9);
+//                           k over two waves 13.9), while they are c at most:
+//                           one more and a unit works through two (2688 x 3072
+//                           -> 3072 is 264 of them: 37.7, k over two waves 24.6;
+//                           7232 x 1152 -> 1152, 261: 18.7 / 14.5);
 //   4 c < t <= 6 c          128-token tiles: 256-token ones would start a second
 //                           round of a few (3072 x 1152 -> 3456: 18.9 against 19.8;
 //                           4096 x 3072 -> 3072: 37.5 / 38.8);
@@ -826,7 +829,8 @@ hipError_t launch(Args a, bool i32out, bool ragged, hipStream_t stream) {
 // the matrix work half: four waves only pay up to t = c (2048 x 1152 -> 1152, t =
 // 288: 9.1 over two waves, 10.1 over four; 1536, t = 216: 7.3 both), two up to 2 c,
 // and to 3 c on k loops under 48 stages (1280 x 1152 -> 3456: 11.9, 256-token tiles
-// 12.3; but 1536 x 3072 -> 3072: 21.2 / 20.1).
+// 12.3; but 1536 x 3072 -> 3072: 21.2 / 20.1); up to 4 c more than c 256-token tiles
+// give way to 128-token ones (2688 x 3072 -> 3072: 30.7 / 23.3, k over two waves 26.4).
 enum Variant { kTile256, kTile128, kSplit4, kSplit2, kVariants };
 // token tile, waves of a workgroup
 constexpr int kVariantTokens[kVariants] = {256, 128, 64, 64};
@@ -834,14 +838,15 @@ constexpr int kVariantWaves[kVariants] = {4, 2, 4, 2};
 template <Fmt F>
 inline Variant pick_variant(int64_t M, int64_t N, int64_t K, int cus) {
     const int64_t t = tile_count(M, 64) * tile_count(N, 128), c = cus, nks = K >> 6;
-    if (tile_count(M, 256) * tile_count(N, 128) >= (int64_t)1 << 24) return kTile128;
+    const int64_t t256 = tile_count(M, 256) * tile_count(N, 128);
+    if (t256 >= (int64_t)1 << 24) return kTile128;
     if constexpr (F == Fmt::F6) {
         if (nks >= 4 && t <= c) return kSplit4;
         if (nks >= 2 && (t <= 2 * c || (t <= 3 * c && nks < 48))) return kSplit2;
-        return t > 4 * c && t <= 6 * c ? kTile128 : kTile256;
+        return t <= 6 * c && (t > 4 * c || t256 > c) ? kTile128 : kTile256;
     }
     if (nks >= 4 && (t <= 2 * c || (nks >= 48 && t <= 5 * c && !(t > 3 * c && t <= 4 * c)))) return kSplit4;
-    if (nks >= 2 && t <= 3 * c) return kSplit2;
+    if (nks >= 2 && (t <= 3 * c || (t <= 4 * c && t256 > c))) return kSplit2;
     if (t > 4 * c && t <= 6 * c) return kTile128;
     return kTile256;
 }

@@ -233,6 +233,10 @@ def test_schedule(lib):
     # 2.25: over two waves, or over four from 48 stages on
     assert schedule(lib, 4096, 1152, 1152)[:2] == [3, 64 * 9]
     assert schedule(lib, 4096, 1152, 4608)[:2] == [2, 64 * 9]
+    # 3.09 and 3.94: 216 tiles of 256 tokens, or where those are more than the compute
+    # units (264), over two waves
+    assert schedule(lib, 2112, 3072, 3072)[:2] == [0, 9 * 24]
+    assert schedule(lib, 2688, 3072, 3072)[:2] == [3, 42 * 24]
     # 4.5 at 72 stages: over four waves; past 6 (the 28-block stack's fc2 at
     # 16384 tokens, the video block's fc2 at 43200, the FLUX-style block's
     # linears) tiles of 256 tokens, 512 workgroups resident
@@ -339,6 +343,7 @@ def test_f6_schedule_rule(lib):
     assert f6_choice(lib, 2048, 1152, 4608) == 2     # 1.13, 72 stages: two halves of 128-token tiles
     assert f6_choice(lib, 4096, 1152, 1152) == 5     # 2.25: over two
     assert f6_choice(lib, 4096, 1152, 4608) == 1     # 2.25, 72 stages: 256-token tiles
+    assert f6_choice(lib, 2688, 3072, 3072) == 6     # 3.94, 264 tiles of 256 tokens: of 128
     assert f6_choice(lib, 8192, 1152, 4608) == 6     # 4.5: 128-token tiles
     assert f6_choice(lib, 4096, 3456, 1152) == 1     # 6.75
     assert f6_choice(lib, 43200, 1152, 4608) == 1    # long k, many tiles

@@ -34,7 +34,8 @@ SHAPES = [(1, 16, 128), (33, 130, 128), (65, 200, 192), (300, 1000, 256), (257, 
           (2100, 2048, 256), (1500, 4000, 192), (2120, 3072, 320), (4000, 2050, 128), (2040, 3968, 3072),
           (1100, 3072, 256), (1100, 3000, 3072), (2100, 4090, 192), (2560, 3072, 3136), (6200, 2000, 256), (6208, 2050, 128),
           (6201, 2048, 128), (4097, 3456, 192), (16384, 1152, 320), (12800, 2176, 768), (2049, 8320, 448),
-          (25700, 1024, 1152), (12801, 1008, 128), (12801, 1040, 128)]
+          (25700, 1024, 1152), (12801, 1008, 128), (12801, 1040, 128),
+          (2688, 3072, 128), (520, 12000, 320), (840, 8605, 3072)]
 
 
 def _codes(clq, fmt, x, w, M, N, K, block):
