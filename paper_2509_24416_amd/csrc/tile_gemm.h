@@ -825,6 +825,10 @@ hipError_t launch(Args a, bool i32out, bool ragged, hipStream_t stream) {
 //   t > 6 c                 256-token tiles, which move the fewest operand bytes
 //                           (43200 x 1152 block: 590 us of GEMM against 690), up
 //                           to 2^24 - 1 of them (a launch has under 2^32 lanes).
+//   and up to 8 c, where 256-token tiles are more than the 2 c resident at once but
+// 128-token ones no more than their 4 c (1907 x 3072 -> 8605, 544 and 1020 tiles: 53.6
+// against 42.3; 14464 x 1152 -> 1152 26.0 / 20.6, fp6 26.1 / 20.1; of W8A8's, 3 c, not:
+// 14464 x 4608 -> 1152 95.1 / 98.1).
 // Splits need a stage for every wave.  fp6 operands are half again as large,
 // the matrix work half: four waves only pay up to t = c (2048 x 1152 -> 1152, t =
 // 288: 9.1 over two waves, 10.1 over four; 1536, t = 216: 7.3 both), two up to 2 c,
@@ -840,14 +844,15 @@ inline Variant pick_variant(int64_t M, int64_t N, int64_t K, int cus) {
     const int64_t t = tile_count(M, 64) * tile_count(N, 128), c = cus, nks = K >> 6;
     const int64_t t256 = tile_count(M, 256) * tile_count(N, 128);
     if (t256 >= (int64_t)1 << 24) return kTile128;
+    const bool one_round = F != Fmt::W8A8 && t256 > 2 * c && tile_count(M, 128) * tile_count(N, 128) <= 4 * c;
     if constexpr (F == Fmt::F6) {
         if (nks >= 4 && t <= c) return kSplit4;
         if (nks >= 2 && (t <= 2 * c || (t <= 3 * c && nks < 48))) return kSplit2;
-        return t <= 6 * c && (t > 4 * c || t256 > c) ? kTile128 : kTile256;
+        return one_round || (t <= 6 * c && (t > 4 * c || t256 > c)) ? kTile128 : kTile256;
     }
     if (nks >= 4 && (t <= 2 * c || (nks >= 48 && t <= 5 * c && !(t > 3 * c && t <= 4 * c)))) return kSplit4;
     if (nks >= 2 && (t <= 3 * c || (t <= 4 * c && t256 > c))) return kSplit2;
-    if (t > 4 * c && t <= 6 * c) return kTile128;
+    if (one_round || (t > 4 * c && t <= 6 * c)) return kTile128;
     return kTile256;
 }
 

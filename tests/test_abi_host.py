@@ -243,6 +243,9 @@ def test_schedule(lib):
     assert schedule(lib, 8192, 1152, 4608)[:2] == [2, 128 * 9]
     assert schedule(lib, 16384, 1152, 4608) == [0, 64 * 9, 64 * 9, 0, 512]
     assert schedule(lib, 43200, 1152, 4608) == [0, 169 * 9, 169 * 9, 0, 512]
+    # 7.95 and 7.98: 513 tiles of 256 tokens, of 128 the 1017 resident, or 1026
+    assert schedule(lib, 14464, 1152, 1152, ws=0) == [1, 113 * 9, 113 * 9, 0, 113 * 9]
+    assert schedule(lib, 14528, 1152, 1152, ws=0)[:2] == [0, 57 * 9]
     for N, K in ((9216, 3072), (3072, 3072), (3072, 12288), (12288, 3072)):
         assert schedule(lib, 4608, N, K)[:2] == [0, 18 * (N // 128)]
     # long k loops never split, wide and shallow ones only past 8 tiles per CU
@@ -347,6 +350,7 @@ def test_f6_schedule_rule(lib):
     assert f6_choice(lib, 8192, 1152, 4608) == 6     # 4.5: 128-token tiles
     assert f6_choice(lib, 4096, 3456, 1152) == 1     # 6.75
     assert f6_choice(lib, 43200, 1152, 4608) == 1    # long k, many tiles
+    assert f6_choice(lib, 14464, 1152, 1152) == 6 and f6_choice(lib, 14528, 1152, 1152) == 1
     # past 6 and 12 stages at most, 18 on many token panels: a persistent grid
     assert f6_choice(lib, 4096, 3456, 768) == 7 and f6_choice(lib, 4096, 3456, 832) == 1
     assert f6_choice(lib, 43200, 3456, 1152) == 7 and f6_choice(lib, 43200, 3456, 1216) == 1

@@ -2,13 +2,14 @@
 
 The kernel follows from t, the 128 x 64 wave tiles of the product (256 compute
 units assumed): the k loop over four waves up to t = 512 (and to 1280 on k
-loops of 48 stages of 64 codes or more), over two up to 768, tiles of 256
-tokens up to 1024, of 128 up to 1536, of 256 beyond; fp6 codes take four waves
-to 256, two to 512 (768 under 48 stages), and two halves of a workgroup from 256
-to 512 on longer k loops, and a persistent grid past 1536 on k loops of at most
-12 or 18 stages (one tile a workgroup, several, tiles that end mid-stream); fewer stages than waves fall through to the next
-choice.  Shapes sit on both sides of each line, with
-ragged token and channel counts and stage counts that leave remainders, for
+loops of 48 stages of 64 codes or more), over two up to 768 (1024 where tiles
+of 256 tokens would be more than 256), tiles of 256 tokens up to 1024, of 128 up
+to 1536 (2048 where they are one round and tiles of 256 more), of 256 beyond;
+fp6 codes take four waves to 256, two to 512 (768 under 48 stages), two halves
+of a workgroup from 256 to 512 on longer k loops, and a persistent grid past
+1536 on k loops of at most 12 or 18 stages (one tile a workgroup, several, tiles
+that end mid-stream); fewer stages than waves fall through to the next choice.
+Shapes sit on both sides of each line, with ragged token and channel counts and stage counts that leave remainders, for
 every code storage.  Sums are integers and exact.  An fp16 output is one
 rounding of fma(p, w_scale, bias), p the fp32 rounding of sum * x_scale:
 within 2^-11 of the value, plus 2^-24 |p w_scale| for p's rounding, plus half
@@ -35,7 +36,7 @@ SHAPES = [(1, 16, 128), (33, 130, 128), (65, 200, 192), (300, 1000, 256), (257, 
           (1100, 3072, 256), (1100, 3000, 3072), (2100, 4090, 192), (2560, 3072, 3136), (6200, 2000, 256), (6208, 2050, 128),
           (6201, 2048, 128), (4097, 3456, 192), (16384, 1152, 320), (12800, 2176, 768), (2049, 8320, 448),
           (25700, 1024, 1152), (12801, 1008, 128), (12801, 1040, 128),
-          (2688, 3072, 128), (520, 12000, 320), (840, 8605, 3072)]
+          (2688, 3072, 128), (520, 12000, 320), (840, 8605, 3072), (14464, 1152, 832)]
 
 
 def _codes(clq, fmt, x, w, M, N, K, block):
