@@ -881,8 +881,9 @@ int f6_schedule_force = 0;
 
 namespace {
 
-// Short k loops with many tiles, past 6 wave tiles (128 x 64) per compute unit: the
-// persistent grid, up to 12 stages, and up to 18 where many token panels make its
+// Short k loops with more 256-token tiles than the two per compute unit resident at
+// once (up to there 4096 x 256 -> 3456, 432 tiles, 0.95): the persistent grid, up to 12
+// stages, and up to 18 where many token panels make its
 // groups 8 panels long.  Time of the tile kernel over this one, each behind its
 // quantizer on operands too large for the caches (in brackets repeated on cached
 // ones): 4096 x 256 -> 4608 1.19 (1.12), 16384 x 256 -> 3456 1.14 (1.16), 28000 x 512 ->
@@ -898,7 +899,7 @@ bool f6_long_groups(int64_t M) {
 }
 bool f6_persistent(int64_t M, int64_t N, int K, int64_t cus) {
     const int64_t tn = tg::tile_count(N, F6Tile::BN), nks = K >> 6;
-    if (nks > (f6_long_groups(M) ? 18 : 12) || tg::tile_count(M, 64) * tn <= 6 * cus) return false;
+    if (nks > (f6_long_groups(M) ? 18 : 12) || tg::tile_count(M, F6Tile::BM) * tn <= 2 * cus) return false;
     if (N % 16 != 0 || 32 * (tn * F6Tile::BN - N) > N) return false;
     return M * N <= 160 << 20 || (nks >= 4 && tg::tile_count(M, F6Tile::BM) % 64 != 0);
 }

@@ -351,8 +351,10 @@ def test_f6_schedule_rule(lib):
     assert f6_choice(lib, 4096, 3456, 1152) == 1     # 6.75
     assert f6_choice(lib, 43200, 1152, 4608) == 1    # long k, many tiles
     assert f6_choice(lib, 14464, 1152, 1152) == 6 and f6_choice(lib, 14528, 1152, 1152) == 1
-    # past 6 and 12 stages at most, 18 on many token panels: a persistent grid
-    assert f6_choice(lib, 4096, 3456, 768) == 7 and f6_choice(lib, 4096, 3456, 832) == 1
+    # over 512 tiles of 256 tokens and 12 stages at most, 18 on many token panels: a
+    # persistent grid
+    assert f6_choice(lib, 4864, 3456, 768) == 7 and f6_choice(lib, 4864, 3456, 832) == 1
+    assert f6_choice(lib, 4608, 3456, 768) == 1
     assert f6_choice(lib, 43200, 3456, 1152) == 7 and f6_choice(lib, 43200, 3456, 1216) == 1
     assert f6_choice(lib, 32768, 3456, 1152) == 1
     assert f6_choice(lib, 4096, 3072, 768) == 6
