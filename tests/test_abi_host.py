@@ -221,7 +221,7 @@ def schedule(lib, M, N, K, ws=1):
 
 def test_schedule(lib):
     # host planning only (no device here: 256 compute units assumed, 512
-    # persistent workgroups)
+    # workgroups of 256-token tiles resident)
     info = (ctypes.c_int64 * 5)()
     assert lib.clq_w4a4_schedule(0, 8, 64, 1, ctypes.cast(info, ctypes.c_void_p)) == SHAPE
     assert lib.clq_w4a4_schedule(8, 8, 96, 1, ctypes.cast(info, ctypes.c_void_p)) == SHAPE
@@ -298,7 +298,7 @@ def test_rq_schedule(lib):
     assert rq_schedule(lib, 1024, 1152, 1152, 32) == [0, 0, 0, 0]             # 36 blocks, 128 lanes: 3 rows
     assert rq_schedule(lib, 1024, 3456, 1152, 32) == [1, 7, 147, 8 * 27]      # 256 lanes: 7 rows
     assert rq_schedule(lib, 1024, 1152, 1152, 64, ws=0)[0] == 0               # no workspace: two launches
-    assert rq_schedule(lib, 43200, 3456, 1152, 64)[0] == 0                    # persistent grid: two launches
+    assert rq_schedule(lib, 43200, 3456, 1152, 64)[0] == 0                    # many tiles: two launches
     assert rq_schedule(lib, 1024, 1000, 1152, 64)[0] == 0                     # N % 16 != 0
     info = (ctypes.c_int64 * 4)()
     assert lib.clq_w4a4_rq_schedule(1024, 1152, 1152, 48, 1, ctypes.cast(info, ctypes.c_void_p)) == BLOCK

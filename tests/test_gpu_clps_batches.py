@@ -34,7 +34,9 @@ def dev(a):
 @pytest.mark.parametrize("M,N,K,block,G,perm,gamma", [
     (40, 70, 512, 32, 7, False, 0.01), (300, 30, 576, 64, 8, True, 0.01), (33, 129, 1024, 128, 9, False, 0.2),
     (33, 300, 1152, 64, 17, True, 0.0), (20, 18, 2048, 128, 3, True, 0.5), (17, 33, 2560, 64, 2, False, 0.01),
-    (9, 40, 4096, 32, 10, True, 0.01), (9, 20, 4160, 64, 9, True, 0.01), (300, 260, 128, 64, 256, False, 0.05)])
+    (9, 40, 4096, 32, 10, True, 0.01), (9, 20, 4160, 64, 9, True, 0.01), (300, 260, 128, 64, 256, False, 0.05),
+    # two chunks per lane, many and few rows
+    (9, 20, 8256, 64, 9, False, 0.01), (9, 300, 8320, 128, 17, True, 0.01), (9, 20, 16384, 32, 10, True, 0.01)])
 def test_batches_and_widths(clq, M, N, K, block, G, perm, gamma):
     print(f"\n[gpu case] {M} x {N} x {K}, block {block}, {G} candidates, perm {perm}", flush=True)
     X = workloads.activations(M, K, "L1", seed=M + G)

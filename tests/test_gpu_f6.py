@@ -161,9 +161,8 @@ def test_f6_linear_row_stride_and_zero_rows(clq):
     assert oracle.err_metric(Y[:16, :N].astype(np.float64), r["y64"], r["p64"], b) <= TOL
 
 
-# 256-token tiles (the first shape) and 128-token tiles (fewer 256-token
-# tiles than compute units), against the int4 persistent and two-halves
-# kernels
+# 256-token tiles (the first shape) and the k loop over two and four waves, against
+# the int4 storage's kernels
 @pytest.mark.parametrize("M,N,K", [(4096, 3456, 1152), (1024, 3456, 1152), (1000, 1152, 4608)])
 def test_f6_matches_int4_fp16_output(clq, M, N, K):
     # the same sums and the same epilogue arithmetic: the int4 path's sums
@@ -219,8 +218,8 @@ def test_f6_argument_errors(clq):
         clq.clq_w4a4_linear_f6(Xq64, xs64, qw64)      # K < 128
 
 
-# every fp6 GEMM schedule (the persistent kernel, the two-halves kernel on
-# 128- and 64-token tiles) on few and many tiles, ragged shapes and short and
+# every fp6 GEMM schedule that the knob forces (256-token tiles, the two-halves
+# kernel on 128- and 64-token tiles) on few and many tiles, ragged shapes and short and
 # long k loops: the same integer sums and the same fp16 bits
 F6_FORCED = [(1024, 1152, 1152), (300, 1000, 640), (1000, 1152, 4608), (4096, 3456, 1152), (8192, 1152, 4608),
              (65, 200, 256), (2, 16, 128), (777, 3072, 3072)]

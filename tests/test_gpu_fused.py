@@ -46,11 +46,11 @@ def host(t):
 
 # (M, N, K, block): 64-token tiles (1024 x 1152), 128-token tiles (1024 x
 # 3456), ragged token counts, long rows (4 rows per item at K = 2048),
-# every Hadamard block, and a shape on the persistent grid (two launches)
+# every Hadamard block, and a shape of many tiles (two launches)
 SHAPES = [(1024, 1152, 1152, 64), (1024, 3456, 1152, 64), (1000, 3456, 1152, 32), (777, 1152, 1152, 128),
           (1024, 1152, 2048, 64), (2048, 1152, 4608, 64), (4096, 1152, 1152, 64), (300, 4608, 1152, 128),
           (33, 1152, 1152, 64), (8192, 3456, 1152, 64)]
-# two launches: the persistent grid (8192 x 3456), items of fewer than 4
+# two launches: many tiles (8192 x 3456), items of fewer than 4
 # rows (K = 4608 at 64-token tiles)
 TWO_LAUNCHES = {(8192, 3456, 1152), (2048, 1152, 4608)}
 

@@ -170,7 +170,7 @@ def test_accum_i32_bitexact(clq, M, N, K, workspace):
     assert np.array_equal(host(acc), oracle.gemm_i32(xc, wc))
 
 
-# Shapes whose persistent schedule splits the k loop of its last rounds over
+# Shapes whose schedule splits the k loop of its last rounds over
 # every workgroup (clq_w4a4_schedule reports split stages), called repeatedly
 # with one workspace: the split sums equal the whole-tile sums bit for bit
 # and the oracle's on sampled rows.  (6400, 3072, 1536): 600 tiles, both
@@ -208,24 +208,34 @@ def test_split_k_exact_and_repeatable(clq, M, N, K):
     assert clq.clq_w4a4_workspace_status(ws) == [0, 0, 0]   # no wait gave up
 
 
-# Few tiles and a long k loop: the two-halves kernel (no split, no workspace use).
+# Few tiles and a long k loop (no split, no workspace use): the automatic choice,
+# and the two-halves kernel on 128- and 64-token tiles, which the schedule knob
+# forces.
 FEW_TILE_SHAPES = [(2048, 1152, 4608), (2000, 1000, 4608), (2048, 640, 8192), (1024, 1152, 4608), (300, 520, 8192)]
 
 
 @pytest.mark.parametrize("M,N,K", FEW_TILE_SHAPES)
 def test_few_tiles_long_k_exact(clq, M, N, K):
     block = 64
-    assert clq.clq_w4a4_schedule(M, N, K)["kernel"] in (1, 2)
+    assert clq.clq_w4a4_schedule(M, N, K)["kernel"] == 2    # k over four waves
     X = workloads.activations(M, K, "L1", seed=M + 7)
     W = workloads.weights(N, K, seed=N + 7)
     b = workloads.bias(N, seed=8)
     qw = clq.clq_quantize_weights(dev(W), block)
     Xq, xs = clq.clq_rotate_quant_act(dev(X), block)
     ref = oracle.linear(X, W, b, block)
-    acc = clq.clq_w4a4_accum_i32(Xq, xs, qw)
-    assert np.array_equal(host(acc), ref["acc"])
-    Y = clq.clq_w4a4_linear(Xq, xs, qw, dev(b))
-    assert oracle.err_metric(host(Y).astype(np.float64), ref["y64"], ref["p64"], b) <= TOL
+    try:
+        for force, kernel in ((0, 2), (3, 1), (4, 2)):
+            clq.clq_debug_set(clq.CLQ_DEBUG_GEMM_SCHEDULE, force)
+            assert clq.clq_w4a4_schedule(M, N, K)["kernel"] == kernel
+            acc = clq.clq_w4a4_accum_i32(Xq, xs, qw)
+            assert np.array_equal(host(acc), ref["acc"]), force
+            Y = clq.clq_w4a4_linear(Xq, xs, qw, dev(b))
+            assert oracle.err_metric(host(Y).astype(np.float64), ref["y64"], ref["p64"], b) <= TOL, force
+            Y = clq.clq_w4a4_linear(Xq, xs, qw)
+            assert oracle.err_metric(host(Y).astype(np.float64), ref["p64"], ref["p64"]) <= TOL, force
+    finally:
+        clq.clq_debug_set(clq.CLQ_DEBUG_GEMM_SCHEDULE, 0)
 
 
 def test_split_k_wait_gives_up_is_reported(clq):
@@ -487,8 +497,8 @@ def test_qweight_save_load_roundtrip(clq, tmp_path):
     assert np.array_equal(host(clq.clq_w4a4_accum_i32(Xq, xs, back)), host(clq.clq_w4a4_accum_i32(Xq, xs, qw)))
 
 
-# Every schedule the GEMM can take (the debug knob forces one: the persistent
-# kernel with and without its split rule, the two-halves kernel on 128- and
+# Every schedule the GEMM can take (the debug knob forces one: 256-token tiles
+# with and without the split rule, the two-halves kernel on 128- and
 # 64-token tiles) gives the same exact integer sums, and fp16 outputs within
 # the tolerance of the oracle, on shapes that the automatic choice sends to
 # each of them: few tiles, a ragged channel edge, a split-k shape and a

@@ -60,3 +60,31 @@ def test_codes_and_scales(clq, M, K, block, with_perm):
         assert np.array_equal(host(s), ref_s), bits
         assert np.array_equal(got[:M], ref_c if bits == 8 else ref_q), bits
         assert not got[M:].any(), bits
+
+
+# weights have a row order of their own, a clamp and a clip ratio: groups per
+# workgroup, one and two chunks per lane, a workgroup per row for few rows and
+# past 16384 columns, ragged row counts
+@pytest.mark.parametrize("with_perm", [False, True])
+@pytest.mark.parametrize("N,K,block", [
+    (1, 64, 32), (2090, 192, 64), (2090, 1152, 128), (1100, 1792, 64), (600, 8192, 128), (33, 8192, 64), (300, 8256, 64),
+    (290, 8320, 128), (129, 8256, 32), (270, 16384, 32), (200, 16384, 64), (70, 16384, 128), (97, 16448, 64),
+    (40, 16448, 32), (35, 32768, 128), (20, 32768, 32)])
+def test_weight_codes_and_scales(clq, N, K, block, with_perm):
+    print(f"\n[gpu case] weights {N} x {K}, block {block}, perm {with_perm}", flush=True)
+    W = workloads.weights(N, K, seed=N + K + block)
+    W[N // 2] = 0
+    perm = workloads.random_perm(K, seed=K) if with_perm else None
+    pd = None if perm is None else dev(perm)
+    rows = (N + 63) // 64 * 64
+    for bits, quant, uns in (
+            (4, clq.clq_quantize_weights, clq.clq_unswizzle_weights),
+            (6, clq.clq_quantize_weights_f6, lambda q: clq.clq_unswizzle_f6(q.wq, rows, K, True)),
+            (8, clq.clq_quantize_weights8, clq.clq_unswizzle_weights8)):
+        for clip in (1.0, 0.71875):
+            qw = quant(dev(W), block, perm=pd, clip_ratio=clip)
+            ref_q, ref_c, ref_s = oracle.quantize_weights(W, block, perm, clip, bits=8 if bits == 8 else 4)
+            got = host(uns(qw))
+            assert np.array_equal(host(qw.w_scale), ref_s), (bits, clip)
+            assert np.array_equal(got[:N], ref_c if bits == 8 else ref_q), (bits, clip)
+            assert not got[N:].any(), (bits, clip)
