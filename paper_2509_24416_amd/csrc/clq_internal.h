@@ -6,6 +6,18 @@
 
 namespace clq {
 
+// Compute units of the first device used (256 if it cannot be asked).
+inline int compute_units() {
+    static const int cus = [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+            n = 256;
+        return n;
+    }();
+    return cus;
+}
+
 // Packed weight layout (opaque to callers, version 2).
 //
 // Rows are cut into units of 32 rows x 64 k codes (1 KB packed), each stored

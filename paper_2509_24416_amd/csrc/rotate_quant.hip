@@ -671,17 +671,6 @@ int pick_groups(int stride, int64_t total_groups, int cus) {
     return best;
 }
 
-int rq_cus() {
-    static const int cus = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-            n = 256;
-        return n;
-    }();
-    return cus;
-}
-
 template <int B, int QB, bool WEIGHT, int NCH>
 hipError_t launch_rq(RqArgs a, hipStream_t stream) {
     const int cpr = a.K >> 3;
@@ -689,7 +678,7 @@ hipError_t launch_rq(RqArgs a, hipStream_t stream) {
     int T;
     if constexpr (NCH == 1) {
         a.stride = cpr;
-        a.groups = pick_groups(cpr, units * 8, rq_cus());
+        a.groups = pick_groups(cpr, units * 8, compute_units());
         while (a.perm != nullptr && a.groups > 1 && (size_t)a.groups * a.K * 8 > kLdsLimit) a.groups >>= 1;
         T = (a.groups * cpr + 63) / 64 * 64;
     } else {
@@ -765,7 +754,7 @@ hipError_t launch_rq_rows8_f6(const RqArgs &a, hipStream_t stream) {
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit);
     if (e != hipSuccess) return e;
     const int64_t nbatch = (a.rows_alloc + kRows8 - 1) / kRows8;
-    hipLaunchKernelGGL(rotate_quant_rows8_f6_kernel, dim3((unsigned)std::min<int64_t>(nbatch, rq_cus())), dim3(T), lds,
+    hipLaunchKernelGGL(rotate_quant_rows8_f6_kernel, dim3((unsigned)std::min<int64_t>(nbatch, compute_units())), dim3(T), lds,
                        stream, a.X, a.ldx, a.rows_valid, a.rows_alloc, nbatch, a.K, a.out, a.scale);
     return hipGetLastError();
 }
@@ -775,7 +764,7 @@ hipError_t launch_rq_width(const RqArgs &a, hipStream_t stream) {
     // (32-bit offsets within a batch)
     if constexpr (B == 64 && QB == 6 && !WEIGHT)
         if (a.perm == nullptr && a.K > 4096 && a.K <= 64 * (kRows8Lanes / kRows8) && a.K != 8 * 9 * 64 &&
-            kRows8 * a.ldx <= INT32_MAX && rows8_fills(a.rows_alloc / kRows8, rq_cus()))
+            kRows8 * a.ldx <= INT32_MAX && rows8_fills(a.rows_alloc / kRows8, compute_units()))
             return launch_rq_rows8_f6(a, stream);
     if (a.batch == 1 && a.rows_alloc <= few_rows<B, QB>(a.K, a.perm != nullptr))
         return launch_rq_wide<B, QB, WEIGHT>(a, stream);

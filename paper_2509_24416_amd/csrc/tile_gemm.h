@@ -97,6 +97,16 @@ __device__ __forceinline__ uint32_t fma_mix2f(float p0, float w0, float b0, floa
     return r;
 }
 
+// the same with the biases as a packed fp16 pair (low half: first output)
+__device__ __forceinline__ uint32_t fma_mix2(float p0, float w0, float p1, float w1, uint32_t b) {
+    uint32_t r;
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[0,0,1]\n\t"
+        "v_fma_mixhi_f16 %0, %4, %5, %3 op_sel:[0,0,1] op_sel_hi:[0,0,1]"
+        : "=&v"(r)
+        : "v"(p0), "v"(w0), "v"(b), "v"(p1), "v"(w1));
+    return r;
+}
+
 // Code storages: bytes of a 32 x 64 unit, and the factor by which the
 // accumulator exceeds the sum of code products (a power of two).
 enum class Fmt { W4A4, F6, W4A8, W8A8 };
@@ -597,7 +607,7 @@ __global__ void __launch_bounds__(C::NT, 2) tile_gemm_kernel(Args a)
 // (L2) to registers, kDepth stages ahead, with no LDS ring and no barrier in
 // the loop.  The sums (exact integers) then meet in LDS by recursive halving:
 // in each step a wave sends half of its fragments to a partner and adds the
-// partner's other half, 28 KB a wave in all for KS = 8, so that every wave ends
+// partner's other half, 16 and 8 KB a wave for KS = 4, so that every wave ends
 // with 8 / KS summed fragments and runs their epilogue.
 template <Fmt F, int KS_>
 struct SplitCfg {
@@ -710,45 +720,24 @@ __global__ void __launch_bounds__(C::NT, 2) split_gemm_kernel(Args a)
             });
         });
     };
-    // step 1 halves by token fragment, the next two by channel fragments.  The
-    // partner of a step differs in one bit of the wave number; the barrier
-    // before a step's sends keeps them behind the last step's receives.
-    auto step3 = [&](auto fn0, auto fm0) __attribute__((always_inline)) {
-        constexpr IC<1> one{};
-        if constexpr (KS == 8) {
-            __syncthreads();
-            constexpr IC<decltype(fn0)::value + 1> fn1{};
-            if ((wave & 1) == 0) {
-                send(fn1, one, fm0, one, wave ^ 1);
-                __syncthreads();
-                receive(fn0, one, fm0, one);
-                finish(fn0, one, fm0, one);
-            } else {
-                send(fn0, one, fm0, one, wave ^ 1);
-                __syncthreads();
-                receive(fn1, one, fm0, one);
-                finish(fn1, one, fm0, one);
-            }
-        } else {
-            finish(fn0, IC<2>{}, fm0, one);
-        }
-    };
+    // step 1 halves by token fragment, step 2 by channel fragments.  The partner of
+    // a step differs in one bit of the wave number; the barrier before a step's
+    // sends keeps them behind the last step's receives.
     auto step2 = [&](auto fm0) __attribute__((always_inline)) {
         constexpr IC<1> one{};
         constexpr IC<2> two{};
-        if constexpr (KS >= 4) {
-            constexpr int bit = KS / 4;
+        if constexpr (KS == 4) {
             __syncthreads();
-            if ((wave & bit) == 0) {
-                send(two, two, fm0, one, wave ^ bit);
+            if ((wave & 1) == 0) {
+                send(two, two, fm0, one, wave ^ 1);
                 __syncthreads();
                 receive(IC<0>{}, two, fm0, one);
-                step3(IC<0>{}, fm0);
+                finish(IC<0>{}, two, fm0, one);
             } else {
-                send(IC<0>{}, two, fm0, one, wave ^ bit);
+                send(IC<0>{}, two, fm0, one, wave ^ 1);
                 __syncthreads();
                 receive(two, two, fm0, one);
-                step3(two, fm0);
+                finish(two, two, fm0, one);
             }
         } else {
             finish(IC<0>{}, IC<4>{}, fm0, one);
@@ -854,17 +843,6 @@ inline Variant pick_variant(int64_t M, int64_t N, int64_t K, int cus) {
     if (nks >= 2 && (t <= 3 * c || (t <= 4 * c && t256 > c))) return kSplit2;
     if (one_round || (t > 4 * c && t <= 6 * c)) return kTile128;
     return kTile256;
-}
-
-inline int compute_units() {
-    static const int cus = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-            n = 256;
-        return n;
-    }();
-    return cus;
 }
 
 // ring depths: at least two workgroups (256 tokens) or three (128) per compute

@@ -51,41 +51,11 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
-template <int Q> using IC = std::integral_constant<int, Q>;
-
-__device__ __forceinline__ uint32_t lds_addr(const void *p) {
-    return (uint32_t)reinterpret_cast<size_t>((CLQ_LDS const void *)p);
-}
-template <int OFF>
-__device__ __forceinline__ v4u lds_read16(uint32_t addr) {
-    v4u v;
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
-    return v;
-}
-template <int OFF>
-__device__ __forceinline__ v2u lds_read8(uint32_t addr) {
-    v2u v;
-    asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
-    return v;
-}
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F &&f) {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
-}
-
-// two fp16 outputs fma(p, w, bias) rounded once from fp32 operands and a
-// packed fp16 bias pair (low half: first output)
-__device__ __forceinline__ uint32_t fma_mix2(float p0, float w0, float p1, float w1, uint32_t b) {
-    uint32_t r;
-    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[0,0,1]\n\t"
-        "v_fma_mixhi_f16 %0, %4, %5, %3 op_sel:[0,0,1] op_sel_hi:[0,0,1]"
-        : "=&v"(r)
-        : "v"(p0), "v"(w0), "v"(b), "v"(p1), "v"(w1));
-    return r;
-}
+using tg::fma_mix2;
+using tg::fma_mix2f;
+using tg::IC;
+using tg::lds_addr;
+using tg::static_for;
 
 constexpr int kUnit = kF6Unit;  // bytes of a 32 x 64 fp6 unit
 constexpr int kGroupM = 8;      // token panels per tile group (L2 reuse of channel panels)
@@ -315,13 +285,13 @@ __global__ void __launch_bounds__(F6Tile::NT, 2) f6_gemm_kernel(F6Args a)
         const uint32_t bx16 = b16 + xo, bx8 = b8 + xo;
         static_for<0, kFN>([&](auto f) {
             constexpr int o = decltype(f)::value * kUnit;
-            ra[P][f] = lds_read16<o>(b16);
-            sa[P][f] = lds_read8<o>(b8);
+            ra[P][f] = tg::read16<o>(b16);
+            sa[P][f] = tg::read8<o>(b8);
         });
         static_for<0, kFM>([&](auto f) {
             constexpr int o = decltype(f)::value * kUnit;
-            rb[P][f] = lds_read16<o>(bx16);
-            sb[P][f] = lds_read8<o>(bx8);
+            rb[P][f] = tg::read16<o>(bx16);
+            sb[P][f] = tg::read8<o>(bx8);
         });
     };
     auto stage_ready = [&](auto pc) __attribute__((always_inline)) {
@@ -533,16 +503,6 @@ struct F6HalfTile {
 using F6Half128 = F6HalfTile<2, 3>;   // 128 x 128 tiles, 72 KB of rings
 using F6Half64 = F6HalfTile<1, 4>;    // 128 x 64 tiles, 72 KB of rings
 
-// the mixed fma of fma_mix2 with fp32 bias operands (each exactly an fp16 value)
-__device__ __forceinline__ uint32_t fma_mix2f(float p0, float w0, float b0, float p1, float w1, float b1) {
-    uint32_t r;
-    asm("v_fma_mixlo_f16 %0, %1, %2, %3\n\t"
-        "v_fma_mixhi_f16 %0, %4, %5, %6"
-        : "=&v"(r)
-        : "v"(p0), "v"(w0), "v"(b0), "v"(p1), "v"(w1), "v"(b1));
-    return r;
-}
-
 template <class C, bool I32OUT, bool RAGGED, bool BIAS>
 __global__ void __launch_bounds__(C::NT, C::NWH == 1 ? 1 : 2) f6_gemm_halves_kernel(F6Args a)
 {
@@ -622,13 +582,13 @@ __global__ void __launch_bounds__(C::NT, C::NWH == 1 ? 1 : 2) f6_gemm_halves_ker
         const uint32_t bx16 = b16 + xo, bx8 = b8 + xo;
         static_for<0, kFN>([&](auto f) {
             constexpr int o = decltype(f)::value * kUnit;
-            ra[P][f] = lds_read16<o>(b16);
-            sa[P][f] = lds_read8<o>(b8);
+            ra[P][f] = tg::read16<o>(b16);
+            sa[P][f] = tg::read8<o>(b8);
         });
         static_for<0, kFM>([&](auto f) {
             constexpr int o = decltype(f)::value * kUnit;
-            rb[P][f] = lds_read16<o>(bx16);
-            sb[P][f] = lds_read8<o>(bx8);
+            rb[P][f] = tg::read16<o>(bx16);
+            sb[P][f] = tg::read8<o>(bx8);
         });
     };
     auto stage_ready = [&](auto pc) __attribute__((always_inline)) {
@@ -848,7 +808,7 @@ namespace {
 hipError_t launch_gemm_f6_persistent(F6Args g, bool i32out, hipStream_t stream) {
     g.tiles_m = (int)tg::tile_count(g.M, F6Tile::BM);
     g.tiles_n = (int)tg::tile_count(g.N, F6Tile::BN);
-    const int full = (tg::compute_units() * 2 + 7) / 8 * 8;
+    const int full = (compute_units() * 2 + 7) / 8 * 8;
     const int grid = std::max(8, (std::min(g.tiles_m * g.tiles_n, full) + 7) / 8 * 8);
     const dim3 gd((unsigned)grid), bd(F6Tile::NT);
     if (i32out) hipLaunchKernelGGL((f6_gemm_kernel<true, false>), gd, bd, 0, stream, g);
@@ -915,7 +875,7 @@ int f6_schedule(int64_t M, int64_t N, int K) {
     // 64 wave tiles per compute unit stay on the two halves, whose four waves
     // share the operands through LDS (2048 x 4608 -> 1152: 18.8 us, 19.4 with the
     // k loop over two waves, 20.6 over four, 25.2 on 256-token tiles).
-    const int64_t waves = (M + 63) / 64 * ((N + 127) / 128), cus = tg::compute_units();
+    const int64_t waves = (M + 63) / 64 * ((N + 127) / 128), cus = compute_units();
     if ((K >> 6) >= 48 && waves > cus && waves <= 2 * cus) return 2;
     if (f6_persistent(M, N, K, cus)) return 7;
     switch (tg::pick_variant<tg::Fmt::F6>(M, N, K, (int)cus)) {

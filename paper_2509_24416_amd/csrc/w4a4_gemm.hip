@@ -73,51 +73,12 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
-template <int Q> using IC = std::integral_constant<int, Q>;
-
-__device__ __forceinline__ uint32_t lds_addr(const void *p) {
-    return (uint32_t)reinterpret_cast<size_t>((CLQ_LDS const void *)p);
-}
-template <int OFF>
-__device__ __forceinline__ v4u lds_read16(uint32_t addr) {
-    v4u v;
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
-    return v;
-}
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F &&f) {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
-}
-
-__device__ __forceinline__ v4i widen16(uint32_t d0, uint32_t d1) {
-    return v4i{(int)((d0 << 4) & 0xF0F0F0F0u), (int)((d1 << 4) & 0xF0F0F0F0u),
-               (int)(d0 & 0xF0F0F0F0u), (int)(d1 & 0xF0F0F0F0u)};
-}
-
-// two fp16 outputs fma(p, w, bias) rounded once from fp32 operands and a
-// packed fp16 bias pair (low half: first output), no separate conversions
-__device__ __forceinline__ uint32_t fma_mix2(float p0, float w0, float p1, float w1, uint32_t b) {
-    uint32_t r;
-    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[0,0,1]\n\t"
-        "v_fma_mixhi_f16 %0, %4, %5, %3 op_sel:[0,0,1] op_sel_hi:[0,0,1]"
-        : "=&v"(r)
-        : "v"(p0), "v"(w0), "v"(b), "v"(p1), "v"(w1));
-    return r;
-}
-
-// the same with fp32 bias operands (each exactly an fp16 value), so that
-// every kernel's outputs are rounded by the same instruction
-__device__ __forceinline__ uint32_t fma_mix2f(float p0, float w0, float b0, float p1, float w1, float b1) {
-    uint32_t r;
-    asm("v_fma_mixlo_f16 %0, %1, %2, %3\n\t"
-        "v_fma_mixhi_f16 %0, %4, %5, %6"
-        : "=&v"(r)
-        : "v"(p0), "v"(w0), "v"(b0), "v"(p1), "v"(w1), "v"(b1));
-    return r;
-}
+using tg::fma_mix2;
+using tg::fma_mix2f;
+using tg::IC;
+using tg::lds_addr;
+using tg::static_for;
+using tg::widen16;
 
 constexpr int kStages = 5;   // ring depth
 constexpr int kGroupM = 4;          // token panels per tile group (L2 reuse of channel panels)
@@ -333,8 +294,8 @@ __global__ void __launch_bounds__(C::NT, C::WGS) w4a4_gemm_kernel(GemmArgs a)
         asm volatile("" : "+v"(wl), "+v"(xl));
         wl += lds_addr(slot(qc));
         xl += lds_addr(slot(qc));
-        static_for<0, C::FN>([&](auto f) { pa[f] = lds_read16<decltype(f)::value * 1024>(wl); });
-        static_for<0, C::FM>([&](auto f) { pb[f] = lds_read16<decltype(f)::value * 1024>(xl); });
+        static_for<0, C::FN>([&](auto f) { pa[f] = tg::read16<decltype(f)::value * 1024>(wl); });
+        static_for<0, C::FM>([&](auto f) { pb[f] = tg::read16<decltype(f)::value * 1024>(xl); });
     };
     auto operands_ready = [&]() {
         static_assert(C::FN == 4 && C::FM == 2, "operand list below");
@@ -870,8 +831,8 @@ __global__ void __launch_bounds__(2 * C::NT, 2) w4a4_gemm_halves_kernel(GemmArgs
         asm volatile("" : "+v"(wl), "+v"(xl));
         wl += lds_addr(&ring[half][q][0]);
         xl += lds_addr(&ring[half][q][0]);
-        static_for<0, C::FN>([&](auto f) { pa[f] = lds_read16<decltype(f)::value * 1024>(wl); });
-        static_for<0, C::FM>([&](auto f) { pb[f] = lds_read16<decltype(f)::value * 1024>(xl); });
+        static_for<0, C::FN>([&](auto f) { pa[f] = tg::read16<decltype(f)::value * 1024>(wl); });
+        static_for<0, C::FM>([&](auto f) { pb[f] = tg::read16<decltype(f)::value * 1024>(xl); });
     };
     auto operands_ready = [&]() {
         static_assert(C::FN == 4 && C::FM == 2, "operand list below");
@@ -1104,20 +1065,9 @@ using TCfg = Tile<1, 4, 4, 2, 2>;
 // the schedule counts channel tiles once for every kernel
 static_assert(TCfg::BN == TileHalf128::BN && TCfg::BN == TileHalf64::BN, "one channel-tile width");
 
-int device_cus() {
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-            cus = 256;
-    }
-    return cus;
-}
-
 // Persistent grid: the workgroups that fit on the chip at once, a multiple of
 // 8 (one equal share per XCD).
-int full_grid() { return (device_cus() * TCfg::WGS + 7) / 8 * 8; }
+int full_grid() { return (compute_units() * TCfg::WGS + 7) / 8 * 8; }
 
 // Splitting the last rounds along k costs each split tile a partial write and
 // read per contributing workgroup (a few microseconds of latency on the
@@ -1193,13 +1143,13 @@ HalvesPlan plan_halves(int64_t M, int64_t N, int K, int force) {
     HalvesPlan p{};
     const int64_t tiles_n = (N + TCfg::BN - 1) / TCfg::BN;
     const int64_t ntiles = (M + TCfg::BM - 1) / TCfg::BM * tiles_n;
-    const bool deep = K >= 2048 && (N < 4 * (int64_t)K || ntiles <= 8 * device_cus());
+    const bool deep = K >= 2048 && (N < 4 * (int64_t)K || ntiles <= 8 * compute_units());
     if ((K >> 6) < kHalvesMinStages || force == 1 || force == 2) return p;
-    if (force == 0 && 4 * ntiles > 5 * device_cus() && !deep) return p;
+    if (force == 0 && 4 * ntiles > 5 * compute_units() && !deep) return p;
     // 128-token tiles (two four-wave workgroups per compute unit), or 64
     // while those would fill at most half the compute units
     const int64_t tm128 = (M + TileHalf128::BM - 1) / TileHalf128::BM;
-    p.kernel = force == 4 || (force != 3 && 2 * tm128 * tiles_n <= device_cus()) ? 2 : 1;
+    p.kernel = force == 4 || (force != 3 && 2 * tm128 * tiles_n <= compute_units()) ? 2 : 1;
     p.tiles_m = p.kernel == 2 ? (M + TileHalf64::BM - 1) / TileHalf64::BM : tm128;
     p.tiles = p.tiles_m * tiles_n;
     return p;
@@ -1218,7 +1168,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int K, bool may_split, int force) {
         p.halves = true;
         p.tiles_m = h.tiles_m;
         p.tiles = p.dp = h.tiles;
-        p.grid = std::min<int64_t>(p.tiles, 2 * device_cus());
+        p.grid = std::min<int64_t>(p.tiles, 2 * compute_units());
         return p;
     }
     if (force >= 3) force = 0;
@@ -1226,12 +1176,12 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int K, bool may_split, int force) {
     p.tiles_m = (M + TCfg::BM - 1) / TCfg::BM;
     p.tiles = p.tiles_m * tiles_n;
     if (may_split && (force == 1 || (force == 0 && h.kernel == 0)) && plan_split(p, K >> 6)) return p;
-    const tg::Variant v = force == 0 ? tg::pick_variant<tg::Fmt::W4A4>(M, N, K, device_cus()) : tg::kTile256;
+    const tg::Variant v = force == 0 ? tg::pick_variant<tg::Fmt::W4A4>(M, N, K, compute_units()) : tg::kTile256;
     p.kernel = v;
     p.tiles_m = tg::tile_count(M, tg::kVariantTokens[v]);
     p.tiles = p.dp = p.tiles_m * tiles_n;
     // (two waves on a SIMD: the kernels take more than half of its registers)
-    p.grid = std::min<int64_t>(p.tiles, (int64_t)device_cus() * 8 / tg::kVariantWaves[v]);
+    p.grid = std::min<int64_t>(p.tiles, (int64_t)compute_units() * 8 / tg::kVariantWaves[v]);
     return p;
 }
 
