@@ -265,7 +265,7 @@ obs_column_kernel(const float *__restrict__ S, int64_t N, int D, int P, float *_
 constexpr int kPermThreads = 1024;
 
 // The swap.  One workgroup; thread t holds channels NP t .. NP t + NP - 1 in
-// registers.  It is bound by its barriers (about 25) and one pass over the
+// registers.  It is bound by its 21 barriers and one pass over the
 // scores, where counting for every channel how many beat it took a clear, a
 // D^2 comparison and a partition launch: 20 -> 7 us at D = 1152, in one launch.
 // Scores compare as floats (the two zeros are equal); a NaN counts as the

@@ -1071,10 +1071,15 @@ int full_grid() { return (compute_units() * TCfg::WGS + 7) / 8 * 8; }
 
 // Splitting the last rounds along k costs each split tile a partial write and
 // read per contributing workgroup (a few microseconds of latency on the
-// critical path), so it is used only when it saves more than that: at least
-// kSplitMinSaved k-stages per workgroup and a sixth of the whole-tile
-// schedule, with shares of at least kSplitMinShare stages (a tile is then
-// summed from at most nks / kSplitMinShare + 1 pieces).
+// critical path).  The line was drawn against whole tiles on this file's
+// persistent kernel: at least kSplitMinSaved k-stages saved per workgroup and a
+// sixth of the whole-tile schedule, with shares of at least kSplitMinShare stages
+// (a tile is then summed from at most nks / kSplitMinShare + 1 pieces).  It keeps
+// the products it had, K from 1152 to 1984 with a badly filled last round;
+// tile_gemm.h's kernels, which a caller without a workspace gets, are the faster
+// at every one measured (us, split / whole: 14848 x 1152 -> 1152 37.6 / 28.1, 16384 x
+// 1920 -> 1152 49.5 / 37.4, 6400 x 1536 -> 3072 46.4 / 32.7, 11264 x 1536 -> 3200 71.1 /
+// 52.2, 10240 x 1984 -> 2048 52.9 / 38.9).
 constexpr int kSplitMinSaved = 16;
 constexpr int kSplitMinShare = 8;
 constexpr int kHalvesMinStages = 4;   // k-stages for the two-halves kernel
