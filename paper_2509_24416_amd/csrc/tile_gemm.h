@@ -795,14 +795,18 @@ hipError_t launch(Args a, bool i32out, bool ragged, hipStream_t stream) {
 //                           is resident at once and the k loop is a quarter as
 //                           long (1024 x 4608 -> 1152: 11.3 us against 22.0 for two
 //                           halves of the workgroup and 26.3 on 256-token tiles;
-//                           1024 x 1152 -> 3456: 9.9 / 11.6 / 12.2);
+//                           1024 x 1152 -> 3456: 9.9 / 11.6 / 12.2;
+//                           3584 x 1152 -> 1152, t = 1.97 c: 9.3, over two waves
+//                           11.2; 3712, 2.04 c: 12.7 / 11.0);
 //   2 c < t <= 3 c          still one round of two-wave workgroups: k over two
 //                           waves (1280 x 1152 -> 3456: 11.8, over four 13.8,
 //                           256-token tiles 12.3), or over four on long k loops,
 //                           which hide the second round (1024 x 3072 -> 9216 is t =
 //                           1152: 31.3 over four, 33.4 on 128-token tiles; 8192 x
 //                           4608 -> 1152: 40.9 / 46.0; 2048 x 3072 -> 3072, t = 768: 21.6,
-//                           22.2 over two), up to t = 5 c;
+//                           22.2 over two), up to t = 5 c (2752 x 3072 -> 3072, 4.03 c:
+//                           30.5, 128-token tiles 33.1; 3392, 4.97 c: 32.1 / 36.5; 3456,
+//                           5.06 c: 35.7 / 36.1, W4A8 40.0 / 38.5);
 //   3 c < t <= 4 c          256-token tiles, half a round (1536 x 1152 -> 4608: 13.4,
 //                           k over two waves 13.9), while they are c at most:
 //                           one more and a unit works through two (2688 x 3072
@@ -810,20 +814,24 @@ hipError_t launch(Args a, bool i32out, bool ragged, hipStream_t stream) {
 //                           7232 x 1152 -> 1152, 261: 18.7 / 14.5);
 //   4 c < t <= 6 c          128-token tiles: 256-token ones would start a second
 //                           round of a few (3072 x 1152 -> 3456: 18.9 against 19.8;
-//                           4096 x 3072 -> 3072: 37.5 / 38.8);
+//                           4096 x 3072 -> 3072: 37.5 / 38.8; 10880 x 1152 -> 1152, 5.98
+//                           c: 18.9 / 19.4; 10944, 6.01 c: 20.0 / 19.6); and up to
+//                           8 c, where 256-token ones are more than the 2 c
+//                           resident at once but 128-token ones no more than their
+//                           4 c (1907 x 3072 -> 8605, 544 and 1020 tiles: 53.6 against
+//                           42.3; 14464 x 1152 -> 1152 26.0 / 20.6, fp6 26.1 / 20.1; not
+//                           of W8A8's, 3 c: 14464 x 4608 -> 1152 95.1 / 98.1);
 //   t > 6 c                 256-token tiles, which move the fewest operand bytes
 //                           (43200 x 1152 block: 590 us of GEMM against 690), up
 //                           to 2^24 - 1 of them (a launch has under 2^32 lanes).
-//   and up to 8 c, where 256-token tiles are more than the 2 c resident at once but
-// 128-token ones no more than their 4 c (1907 x 3072 -> 8605, 544 and 1020 tiles: 53.6
-// against 42.3; 14464 x 1152 -> 1152 26.0 / 20.6, fp6 26.1 / 20.1; of W8A8's, 3 c, not:
-// 14464 x 4608 -> 1152 95.1 / 98.1).
 // Splits need a stage for every wave.  fp6 operands are half again as large,
 // the matrix work half: four waves only pay up to t = c (2048 x 1152 -> 1152, t =
-// 288: 9.1 over two waves, 10.1 over four; 1536, t = 216: 7.3 both), two up to 2 c,
-// and to 3 c on k loops under 48 stages (1280 x 1152 -> 3456: 11.9, 256-token tiles
-// 12.3; but 1536 x 3072 -> 3072: 21.2 / 20.1); up to 4 c more than c 256-token tiles
-// give way to 128-token ones (2688 x 3072 -> 3072: 30.7 / 23.3, k over two waves 26.4).
+// 288: 9.1 over two waves, 10.1 over four; 1536, t = 216: 7.3 both; 1792, 0.98 c: 6.7
+// both; 1856, 1.02 c: 8.3 / 9.3), two up to 2 c, and to 3 c on k loops under 48
+// stages (1280 x 1152 -> 3456: 11.9, 256-token tiles 12.3; but 1536 x 3072 -> 3072: 21.2
+// / 20.1; 5440 x 1152 -> 1152, 2.99 c: 11.9 / 12.1; 5504, 3.02 c: 13.5 / 12.1); up to 4 c
+// more than c 256-token tiles give way to 128-token ones (2688 x 3072 -> 3072: 30.7 /
+// 23.3, k over two waves 26.4).
 enum Variant { kTile256, kTile128, kSplit4, kSplit2, kVariants };
 // token tile, waves of a workgroup
 constexpr int kVariantTokens[kVariants] = {256, 128, 64, 64};
